@@ -35,6 +35,10 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+// Global memory reached through a pointer whose origin the compiler cannot see.
+typedef __attribute__((address_space(1))) float GlobalFloat;
+typedef __attribute__((address_space(1))) f32x4_t GlobalFloat4;
 
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr int kAwPitch = 132;  // floats per row of a wave's partial accumulator
@@ -63,6 +67,28 @@ __device__ __forceinline__ float row16_sum(float x) {
   v = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false); // row_ror:8
   x += __int_as_float(v);
   return x;
+}
+
+__device__ __forceinline__ float row16_max(float x) {
+  int v;
+  v = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xf, 0xf, false);
+  x = fmaxf(x, __int_as_float(v));
+  v = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xf, 0xf, false);
+  x = fmaxf(x, __int_as_float(v));
+  v = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, false);
+  x = fmaxf(x, __int_as_float(v));
+  v = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false);
+  return fmaxf(x, __int_as_float(v));
+}
+// Sum / max with the lane 16 away (l ^ 16): swapping the odd rows of one copy
+// with the even rows of another leaves the pair's two values in the results.
+__device__ __forceinline__ float x16_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float x16_max(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Max / sum across the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48).
@@ -1110,114 +1136,169 @@ __global__ void __launch_bounds__(64) clear_counters_kernel(uint32_t *c, int n) 
 //   * merge the split slots the history calls wrote (Eq. 14; slot count per
 //     request from the host, unwritten slots are never read),
 //   * write O = a / l and LSE = m ln 2 + ln l (Eq. 17).
-// One wave per row (4 rows of one request per workgroup); lane l
-// holds d = 2l, 2l+1.  The kernel is latency-bound, so a row costs one
-// memory round trip: every load is issued before any use (the query, the
-// visible candidates' K/V, each slot's m and l - lane s loads slot s - and
-// every slot's a values).  The row's maximum over the frontier scores and
-// the slot maxima then gives each term its scale 2^(m_s - m*) once (Eq. 14
-// applied to all pieces together), so the slots need no step-by-step
-// rescaling.  Slot loads past the request's count go through empty buffer
-// resources or offsets past the end and read zeros.
-// ---------------------------------------------------------------------------
 //
-// The grid is (request, block of 4 rows), sized for the request with the
-// most rows; a block past a request's rows exits at once.  Workgroups are
-// dispatched in grid order, so with the requests as the fast dimension the
-// blocks of the requests with the most rows come last, behind every idle
-// block: with ragged row counts the grid is built the other way round
-// (RowsFast), which spreads the idle blocks over the dispatch.
-template <int MS, bool RowsFast, typename P>
+// The kernel is latency-bound, so a row costs one round trip for the kernel
+// arguments, one for memory, and few instructions.  Half a wave takes a row;
+// lane t of the half holds d = 4t .. 4t+3, so one load instruction brings a
+// slot's values of two rows.  The grid is (block of heads, candidate): a
+// candidate's word gives its index within the request and the request's slot
+// count, so no lane divides and no workgroup is idle.  Every vector load is
+// issued before any use: the query, the candidates' K/V (rows past the causal
+// mask lie past the buffer's end and read zero), each slot's m and l (lane s
+// loads slot s) and every slot's a values (slots past the count read zero).
+// Lane sums and maxima go through DPP and permlane swaps, not LDS.  The
+// maximum over the frontier scores and the slot maxima gives each term its
+// scale 2^(m_s - m*) once (Eq. 14 applied to all pieces together); the slots'
+// scales reach all lanes through LDS.  Against one row per wave, with the row
+// found by two divisions after a second round trip for the arguments, 64
+// ragged requests (269 candidates x 32 heads, 16 slots) went from 11.4 to 8.3
+// us, 128 candidates x 64 heads (4 slots) from 10.6 to 7.5 us.
+//
+// Split = 1: a workgroup's four waves take four pairs of heads.  Split = 4:
+// the four waves take a quarter of the slots and of the candidates of one
+// pair, and merge (Eq. 14) through LDS.  A CU's L1 delivers 64 bytes a cycle:
+// a pair's 32 slots are 32 KiB, 0.25 us of it, and with four pairs on a CU a
+// small round waits 1 us for its loads to go out.  The split also quarters a
+// wave's instructions, at the price of a barrier and of four times the waves.
+// ---------------------------------------------------------------------------
+template <int MS, int Split, bool Huge, typename P>
 __global__ void __launch_bounds__(256) finalize_kernel(const P p) {
-  const int w = threadIdx.x >> 6;
+  constexpr int kSlots = MS / Split, kCand = kMaxCand / Split;   // slots and candidates of a wave
+  __shared__ __attribute__((aligned(16))) float scale_sh[kWaves][2][32];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const Item it = p.items[RowsFast ? blockIdx.y : blockIdx.x];
-  const int r = (RowsFast ? blockIdx.x : blockIdx.y) * kWaves + w;   // local row = i * Hq + h
-  if (r >= it.n_cand * p.Hq) return;
-  const int i = r / p.Hq;
-  const int h = r - i * p.Hq;
-  const int g = h / p.G;
-  const int row = __builtin_amdgcn_readfirstlane(it.q_row0 * p.Hq + r);   // (off_b + i) * Hq + h
-  const int nslot = it.tok_count;
+  const int half = lane >> 5, t = lane & 31;
+  const uint32_t c = blockIdx.y;
+  // every kernel argument, read in one scalar round trip
+  uint32_t pair = p.cand[c >> 1], cand0 = (uint32_t)p.cand0, g_magic = p.g_magic, g_mask = p.g_mask;
+  uint32_t R = (uint32_t)p.st.R, Hq = (uint32_t)p.Hq, kstep = (uint32_t)p.Hkv * kRowBytes;
+  float scale_log2 = p.scale_log2;
+  const uint16_t *q_ptr = p.q, *k_ptr = p.kc, *v_ptr = p.vc;
+  float *m_ptr = p.st.m, *l_ptr = p.st.l, *a_ptr = p.st.a;
+  GlobalFloat *out = (GlobalFloat *)p.out, *lse = (GlobalFloat *)p.lse;
+  asm volatile("" : "+s"(pair), "+s"(cand0), "+s"(g_magic), "+s"(g_mask), "+s"(R), "+s"(Hq), "+s"(kstep), "+s"(q_ptr),
+               "+s"(k_ptr), "+s"(v_ptr), "+s"(m_ptr), "+s"(l_ptr), "+s"(a_ptr), "+s"(out), "+s"(lse), "+s"(scale_log2));
+  const uint32_t word = pair >> (16 * (c & 1));
+  const uint32_t i = word & 7u, nslot = (word >> 3) & 0x3fu;
+  const uint32_t cg = cand0 + c;                                   // packed candidate row
+  const uint32_t h = Split == 1 ? 2 * (blockIdx.x * kWaves + w) + half : 2 * blockIdx.x + half;
+  const uint32_t hc = h < Hq ? h : Hq - 1;                         // lanes past the heads redo the last one
+  const uint32_t g = __umulhi(hc, g_magic) + (hc & g_mask);        // hc / G
+  const uint32_t row = cg * Hq + hc;
+  const uint32_t s0 = Split == 1 ? 0 : w * kSlots, j0 = Split == 1 ? 0 : w * kCand;   // the wave's first slot, candidate
 
-  const uint32_t qw = reinterpret_cast<const uint32_t *>(p.q + (size_t)row * kHeadDim)[lane];
-  uint32_t kw[kMaxCand], vw[kMaxCand];
+  auto rsrc = [](const void *base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, kBufferFlags);
+  };
+  // resources over the candidates 0..i of the request and all before it
+  const __amdgpu_buffer_rsrc_t krs = rsrc(k_ptr, (cg + 1) * kstep), vrs = rsrc(v_ptr, (cg + 1) * kstep);
+  const __amdgpu_buffer_rsrc_t qrs = rsrc(q_ptr, R * kRowBytes);
+  const uint32_t koff = (cg - i + j0) * kstep + g * kRowBytes + 8 * t;
+  const u32x2_t qw = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(qrs, row * kRowBytes + 8 * t, 0, 0));
+  u32x2_t kw[kCand], vw[kCand];
 #pragma unroll
-  for (int j = 0; j < kMaxCand; ++j) {
-    kw[j] = 0;
-    vw[j] = 0;
-    if (j <= i) {
-      const size_t kv = ((size_t)(it.q_row0 + j) * p.Hkv + g) * kHeadDim;
-      kw[j] = reinterpret_cast<const uint32_t *>(p.kc + kv)[lane];
-      vw[j] = reinterpret_cast<const uint32_t *>(p.vc + kv)[lane];
-    }
-  }
-  // slot s's m and l in lane s (offsets past the array read zero)
-  const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc(
-      p.st.m, (short)0, (int)((uint32_t)kNumSlots * (uint32_t)p.st.R * 4), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t lrs = __builtin_amdgcn_make_buffer_rsrc(
-      p.st.l, (short)0, (int)((uint32_t)kNumSlots * (uint32_t)p.st.R * 4), kBufferFlags);
-  const uint32_t moff = lane < nslot ? ((uint32_t)lane * (uint32_t)p.st.R + (uint32_t)row) * 4 : 0xfffffff0u;
+  for (int j = 0; j < kCand; ++j)
+    kw[j] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(krs, koff + j * kstep, 0, 0));
+  // slot s0 + t's m and l in lane t (slots past the count read zero)
+  const __amdgpu_buffer_rsrc_t mrs = rsrc(m_ptr, nslot * R * 4), lrs = rsrc(l_ptr, nslot * R * 4);
+  const uint32_t moff = ((s0 + t) * R + row) * 4;
   const float m_lane = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, moff, 0, 0));
   const float l_lane = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, moff, 0, 0));
-  // every slot's a values of this row: slot s through a resource over the
-  // row's 512 bytes in that slot (empty past the count); the launch is built
-  // for MS >= every request's slot count
-  float2 as[MS];
+  // the a values of this row in the wave's slots; the launch is built for MS
+  // >= every request's slot count.  One resource over the request's slots
+  // while all slots lie below 2^32 bytes (Huge: one per slot).
+  const uint32_t slot_bytes = R * (kHeadDim * 4);
+  const uint32_t aoff = row * (kHeadDim * 4) + 16 * t;
+  f32x4_t as[kSlots];
+  if constexpr (Huge) {
 #pragma unroll
-  for (int s = 0; s < MS; ++s) {
-    const float *base = p.st.a + ((size_t)s * p.st.R + row) * kHeadDim;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(base), (short)0, s < nslot ? kRowBytes * 2 : 0, kBufferFlags);
-    const uint64_t v = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(rs, (uint32_t)lane * 8, 0, 0));
-    as[s] = __builtin_bit_cast(float2, v);
+    for (int s = 0; s < kSlots; ++s) {
+      const __amdgpu_buffer_rsrc_t ars = rsrc(a_ptr + (size_t)s * R * kHeadDim, (uint32_t)s < nslot ? slot_bytes : 0u);
+      as[s] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(ars, aoff, 0, 0));
+    }
+  } else {
+    const __amdgpu_buffer_rsrc_t ars = rsrc(a_ptr, nslot * slot_bytes);
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s)
+      as[s] = __builtin_bit_cast(f32x4_t,
+                                 __builtin_amdgcn_raw_buffer_load_b128(ars, aoff + (s0 + s) * slot_bytes, 0, 0));
   }
+#pragma unroll
+  for (int j = 0; j < kCand; ++j)
+    vw[j] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(vrs, koff + j * kstep, 0, 0));
+  __builtin_amdgcn_sched_barrier(0);   // every load is out before the first use
 
-  // frontier scores: the <= 8 dot products reduced as independent chains
-  const float q0 = bf16_lo(qw), q1 = bf16_hi(qw);
-  float x[kMaxCand];
+  // frontier scores: the dot products reduced over the half wave as independent chains
+  const float q0 = bf16_lo(qw[0]), q1 = bf16_hi(qw[0]), q2 = bf16_lo(qw[1]), q3 = bf16_hi(qw[1]);
+  float x[kCand];
 #pragma unroll
-  for (int j = 0; j < kMaxCand; ++j) x[j] = fmaf(q0, bf16_lo(kw[j]), q1 * bf16_hi(kw[j]));
+  for (int j = 0; j < kCand; ++j) {
+    float d = fmaf(q1, bf16_hi(kw[j][0]), q0 * bf16_lo(kw[j][0]));
+    d = fmaf(q2, bf16_lo(kw[j][1]), d);
+    x[j] = row16_sum(fmaf(q3, bf16_hi(kw[j][1]), d));
+  }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-    for (int j = 0; j < kMaxCand; ++j) x[j] += __shfl_xor(x[j], off);
+  for (int j = 0; j < kCand; ++j) x[j] = x16_sum(x[j]);
   float m = kNegInf;
 #pragma unroll
-  for (int j = 0; j < kMaxCand; ++j) {
-    x[j] = j <= i ? x[j] * p.scale_log2 : kNegInf;
+  for (int j = 0; j < kCand; ++j) {
+    x[j] = j0 + j <= i ? x[j] * scale_log2 : kNegInf;
     m = fmaxf(m, x[j]);
   }
-  // m* over the frontier (finite: every query sees candidate 0) and the slots
-  const float ms_lane = lane < nslot ? m_lane : kNegInf;
-  float mslot = ms_lane;
+  // m* over the frontier and the slots: finite with Split = 1, where every
+  // query sees candidate 0; a wave of a split row may hold neither
+  const float ms_lane = t < kSlots && s0 + t < nslot ? m_lane : kNegInf;
+  m = fmaxf(m, x16_max(row16_max(ms_lane)));
+  const float mb = Split > 1 && m == kNegInf ? 0.f : m;
+  const float f_lane = exp2_fast(ms_lane - mb);    // slot scale in lane t; 0 past the count
+  scale_sh[w][half][t] = f_lane;
+  float l = x16_sum(row16_sum(f_lane * l_lane));
+  f32x4_t a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mslot = fmaxf(mslot, __shfl_xor(mslot, off));
-  m = fmaxf(m, mslot);
-  const float f_lane = exp2_fast(ms_lane - m);    // slot scale in lane s; 0 past the count
-  float lsum = f_lane * l_lane;
+  for (int j = 0; j < kCand; ++j) {
+    // past the mask the weight is 2^-inf = 0 and the value row zero
+    const float pj = exp2_fast(x[j] - mb);
+    l += pj;
+    a[0] = fmaf(pj, bf16_lo(vw[j][0]), a[0]);
+    a[1] = fmaf(pj, bf16_hi(vw[j][0]), a[1]);
+    a[2] = fmaf(pj, bf16_lo(vw[j][1]), a[2]);
+    a[3] = fmaf(pj, bf16_hi(vw[j][1]), a[3]);
+  }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
-  float l = 0.f, a0 = 0.f, a1 = 0.f;
+  for (int s = 0; s < kSlots; ++s) {
+    const float f = scale_sh[w][half][s];          // the wave's own writes
 #pragma unroll
-  for (int j = 0; j < kMaxCand; ++j) {
-    if (j <= i) {
-      const float pj = exp2_fast(x[j] - m);
-      l += pj;
-      a0 = fmaf(pj, bf16_lo(vw[j]), a0);
-      a1 = fmaf(pj, bf16_hi(vw[j]), a1);
+    for (int k = 0; k < 4; ++k) a[k] = fmaf(f, as[s][k], a[k]);
+  }
+  if constexpr (Split > 1) {
+    __shared__ __attribute__((aligned(16))) f32x4_t a_sh[kWaves][64];
+    __shared__ float2 ml_sh[kWaves][2];
+    a_sh[w][lane] = a;
+    if (t == 0) ml_sh[w][half] = make_float2(m, l);
+    __syncthreads();
+    if (w != 0) return;
+    float2 ml[kWaves];
+    m = kNegInf;
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) {
+      ml[v] = ml_sh[v][half];
+      m = fmaxf(m, ml[v].x);                       // finite: wave 0 holds candidate 0
+    }
+    l = 0.f;
+    a = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) {
+      const float f = exp2_fast(ml[v].x - m);
+      const f32x4_t av = a_sh[v][lane];
+      l = fmaf(f, ml[v].y, l);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] = fmaf(f, av[k], a[k]);
     }
   }
-  l += lsum;
-#pragma unroll
-  for (int s = 0; s < MS; ++s) {
-    const float f = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f_lane), s));
-    a0 = fmaf(f, as[s].x, a0);
-    a1 = fmaf(f, as[s].y, a1);
-  }
+  if (h >= Hq) return;
   const float inv = 1.0f / l;
-  reinterpret_cast<float2 *>(p.out + (size_t)row * kHeadDim)[lane] = make_float2(a0 * inv, a1 * inv);
-  if (p.lse != nullptr && lane == 0) p.lse[row] = m * 0.69314718055994531f + logf(l);
+  *(GlobalFloat4 *)(out + (size_t)row * kHeadDim + 4 * t) = a * inv;
+  if (lse != nullptr && t == 0) lse[row] = m * 0.69314718055994531f + logf(l);
 }
 
 // Read-bandwidth probe: workgroup w XOR-folds the 32-bit words of bytes
@@ -1269,7 +1350,6 @@ namespace {
 // items), large ragged batches the medium one.
 using ChunkSmall = ChunkParamsT<128, 256, 128>;
 using ChunkMedium = ChunkParamsT<512, 1024, 256>;
-using FinalSmall = FinalParamsT<64>;
 
 template <bool Wide, typename D>
 hipError_t launch_chunk_as(const ChunkParams &p, hipStream_t s) {
@@ -1308,52 +1388,106 @@ hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t s) {
   hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, n);
   return hipGetLastError();
 }
-template <int MS, bool RowsFast>
-hipError_t launch_finalize_as(const FinalParams &p, int row_blocks, hipStream_t s) {
-  const dim3 grid = RowsFast ? dim3(row_blocks, p.num_items) : dim3(p.num_items, row_blocks);
-  if (p.num_items <= FinalSmall::kItems) {
-    static thread_local FinalSmall d;
-    static_cast<FinalHeader &>(d) = p;
-    std::memcpy(d.items, p.items, sizeof(Item) * p.num_items);
-    hipLaunchKernelGGL((finalize_kernel<MS, RowsFast, FinalSmall>), grid, dim3(256), 0, s, d);
-  } else {
-    hipLaunchKernelGGL((finalize_kernel<MS, RowsFast, FinalParams>), grid, dim3(256), 0, s, p);
-  }
+namespace {
+
+// What finalize_kernel reads: candidate c's word holds its index within its
+// request (3 bits) and the request's slot count (6 bits), two per dword.
+template <int MaxCand>
+struct FinalArgs : FinalHeader {
+  static constexpr int kCand = MaxCand;
+  int32_t cand0;      // packed candidate row of the launch's first candidate
+  uint32_t g_magic;   // h / G = mulhi(h, g_magic) + (h & g_mask): ceil(2^32 / G) and 0, or 0 and ~0 for G = 1
+  uint32_t g_mask;
+  uint32_t cand[MaxCand / 2];
+};
+using FinalSmall = FinalArgs<128>;
+using FinalLarge = FinalArgs<4096>;
+static_assert(kMaxCand <= 8 && kNumSlots <= 32, "candidate word fields, a lane per slot");
+
+template <int MS, int Split, bool Huge, typename D>
+hipError_t launch_finalize_as(const D &d, int n, hipStream_t s) {
+  constexpr int kHeads = Split == 1 ? 2 * kWaves : 2;   // heads per workgroup
+  hipLaunchKernelGGL((finalize_kernel<MS, Split, Huge, D>), dim3((d.Hq + kHeads - 1) / kHeads, n), dim3(256), 0, s, d);
   return hipGetLastError();
 }
 
-template <int MS>
-hipError_t launch_finalize_ms(const FinalParams &p, int row_blocks, bool rows_fast, hipStream_t s) {
-  return rows_fast ? launch_finalize_as<MS, true>(p, row_blocks, s) : launch_finalize_as<MS, false>(p, row_blocks, s);
+// Built for 8, 16 or 32 slots: each slot a row may read costs the wave a load
+// and four registers, so a launch takes the smallest build that holds every
+// request's slot count.
+template <int Split, typename D>
+hipError_t launch_finalize_split(const D &d, int n, int slots, hipStream_t s) {
+  if (slots <= 8) return launch_finalize_as<8, Split, false>(d, n, s);
+  if (slots <= 16) return launch_finalize_as<16, Split, false>(d, n, s);
+  return launch_finalize_as<kNumSlots, Split, false>(d, n, s);
 }
 
+// Rows are split over a workgroup's waves while that takes at most this many
+// workgroups (4 per CU): below, the chip is not full and the shorter chain
+// wins; above, four times the waves cost more than it.  Rounds back to back,
+// split against not: 1 x 16384 tokens (80 workgroups) 19.6 against 20.8 us,
+// 6 candidates x 32 heads (96) 32.3 against 33.3 us, 8 x 8191 (32) 45.5
+// against 45.9 us, 4 x 16384 x 48 heads (768) 55.8 against 55.9 us; 24 ragged
+// requests (1888) 27.3 against 27.1 us, and 128 candidates x 64 heads (4096)
+// 8.9 against 7.5 us for the launch alone.
+constexpr long kSplitWgs = 1024;
+
+template <typename D>
+hipError_t launch_finalize_cand(const D &d, int n, int slots, hipStream_t s) {
+  if ((uint64_t)kNumSlots * (uint32_t)d.st.R * (kHeadDim * 4) >= (uint64_t(1) << 32))
+    return launch_finalize_as<kNumSlots, 1, true>(d, n, s);
+  if constexpr (D::kCand <= FinalSmall::kCand)
+    if ((long)n * ((d.Hq + 1) / 2) <= kSplitWgs) return launch_finalize_split<4>(d, n, slots, s);
+  return launch_finalize_split<1>(d, n, slots, s);
+}
+
+}  // namespace
+
 hipError_t launch_finalize(const FinalParams &p, hipStream_t s) {
-  // Built for 8, 16, 24 or 32 slots: each slot a row may read costs the
-  // wave a load and two registers, so the smallest build that holds every
-  // request's slot count keeps more waves resident.  Measured on MI355X:
-  // 16 x 32768 tokens (14 slots) 7.3 -> 6.0 us, 64 ragged requests (16
-  // slots) 19.8 -> 13.6 us against the 32-slot build.
-  // Row-block order: the requests-fast grid keeps a request's blocks on one
-  // XCD (the grid's request count is a multiple of 8 in the common case),
-  // which measured faster for uniform cohorts; with more than a quarter of
-  // the blocks idle the rows-fast grid is faster.  Measured on MI355X
-  // (medians, alternated in one run): 64 ragged requests (42% idle) 16.5 us
-  // requests-fast, 14.5-14.9 us rows-fast; 16 x 6 candidates 6.8-7.0 us
-  // requests-fast, 7.0-7.1 us rows-fast.
-  int rows = 0, slots = 0;
-  long busy = 0;
-  for (int i = 0; i < p.num_items; ++i) {
-    const int ri = p.items[i].n_cand * p.Hq;
-    rows = rows > ri ? rows : ri;
-    busy += (ri + kWaves - 1) / kWaves;
-    slots = slots > p.items[i].tok_count ? slots : p.items[i].tok_count;
+  // Candidates in packed order, at most FinalLarge::kCand per launch.  The
+  // words are gathered here; a launch passes the small table when it fits.
+  static thread_local FinalSmall ds;
+  static thread_local FinalLarge dl;
+  // h * (G ceil(2^32 / G) - 2^32) < 2^23 * 64 < 2^32, so mulhi gives h / G exactly
+  const uint32_t magic = p.G > 1 ? (uint32_t)(((uint64_t(1) << 32) + p.G - 1) / p.G) : 0u;
+  int n = 0, slots = 0, c0 = p.num_items > 0 ? p.items[0].q_row0 : 0;
+  auto flush = [&]() {
+    if (n == 0) return hipSuccess;
+    hipError_t e;
+    if (n <= FinalSmall::kCand) {
+      static_cast<FinalHeader &>(ds) = p;
+      ds.cand0 = c0;
+      ds.g_magic = magic;
+      ds.g_mask = p.G > 1 ? 0u : ~0u;
+      std::memcpy(ds.cand, dl.cand, sizeof(uint32_t) * ((n + 1) / 2));
+      e = launch_finalize_cand(ds, n, slots, s);
+    } else {
+      static_cast<FinalHeader &>(dl) = p;
+      dl.cand0 = c0;
+      dl.g_magic = magic;
+      dl.g_mask = p.G > 1 ? 0u : ~0u;
+      e = launch_finalize_cand(dl, n, slots, s);
+    }
+    c0 += n;
+    n = slots = 0;
+    return e;
+  };
+  for (int b = 0; b < p.num_items; ++b) {
+    const Item &it = p.items[b];
+    for (int i = 0; i < it.n_cand; ++i) {
+      if (n == FinalLarge::kCand) {
+        const hipError_t e = flush();
+        if (e != hipSuccess) return e;
+      }
+      const uint32_t word = (uint32_t)i | ((uint32_t)it.tok_count << 3);
+      if (n & 1)
+        dl.cand[n >> 1] |= word << 16;
+      else
+        dl.cand[n >> 1] = word;
+      ++n;
+      slots = slots > it.tok_count ? slots : it.tok_count;
+    }
   }
-  const int row_blocks = (rows + kWaves - 1) / kWaves;
-  const bool rows_fast = 4 * busy < 3 * (long)row_blocks * p.num_items;
-  if (slots <= 8) return launch_finalize_ms<8>(p, row_blocks, rows_fast, s);
-  if (slots <= 16) return launch_finalize_ms<16>(p, row_blocks, rows_fast, s);
-  if (slots <= 24) return launch_finalize_ms<24>(p, row_blocks, rows_fast, s);
-  return launch_finalize_ms<kNumSlots>(p, row_blocks, rows_fast, s);
+  return flush();
 }
 
 hipError_t launch_read_probe(const void *buf, uint64_t bytes, uint64_t share, uint32_t *sink, int workgroups,
