@@ -34,6 +34,7 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 // Global memory reached through a pointer whose origin the compiler cannot see.
@@ -91,17 +92,19 @@ __device__ __forceinline__ float x16_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// The same with the lane 32 away (l ^ 32).
+__device__ __forceinline__ float x32_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float x32_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // Max / sum across the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48).
-__device__ __forceinline__ float xgroup_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  x = fmaxf(x, __shfl_xor(x, 32));
-  return x;
-}
-__device__ __forceinline__ float xgroup_sum(float x) {
-  x += __shfl_xor(x, 16);
-  x += __shfl_xor(x, 32);
-  return x;
-}
+__device__ __forceinline__ float xgroup_max(float x) { return x32_max(x16_max(x)); }
+__device__ __forceinline__ float xgroup_sum(float x) { return x32_sum(x16_sum(x)); }
 
 template <typename P>
 __device__ __forceinline__ int global_row(const P &p, int q_row0, int g, int r) {
@@ -590,61 +593,85 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
 }
 
 // ---------------------------------------------------------------------------
-// Row-split MFMA body for wide query groups (33..64 rows per KV head).  Wave
-// w owns rows 16w .. 16w+15 and attends every tile of the unit, so no
-// cross-wave merge is needed: a wave holds one 16-row block of accumulators
-// and its query operand in registers, and the wide kernel keeps two
-// workgroups per CU.  The four waves stage each 32-token tile together
-// (wave w loads tokens 8w .. 8w+7 of K and of V) into one of two LDS tile
-// buffers, with one workgroup barrier per tile; each wave keeps the loads of
-// the next kRowsAhead tiles in flight in registers.  Per tile a wave runs
-// the one-block math of the body above (same LDS swizzle and operand
-// layouts): S^T = K Q^T, the online softmax, O^T += V^T P^T with P as hi + lo.
+// Row-split MFMA body for wide query groups (33..64 rows per KV head).  The
+// four waves attend 64 tokens (two 32-token tiles) a step: wave w owns rows
+// 32 (w / 2) .. +31 and the tiles 2k + w % 2 of the unit's chain, and the two
+// waves of a row block merge their states once, at the unit's end.  Per step
+// a wave runs v_mfma_f32_32x32x16_bf16: S^T = K Q^T (8 of them, Q in
+// registers), the online softmax (a row's 32 scores lie in the two lanes l,
+// l ^ 32), O^T += V^T P^T with P as hi + lo (16).  What bounds the body is
+// the matrix, vector and LDS work that a step puts behind its barrier, and
+// the shader clock that sustained work of this kind leaves (1.6-1.7 GHz).
+// Every K and V byte is read from LDS by two waves; with 16 rows per wave and
+// 32 tokens a step (v_mfma_f32_16x16x32_bf16) it was read by four, with twice
+// the barriers and row maxima per token.  Rounds back to back, that body
+// against this one: 16 x 32768 tokens with 64 rows 349 -> 339 us (LDS busy
+// 0.62 of before, VALU 0.88), 4 x 16384 with 48 rows 56.3 -> 53.7 us, 1 x
+// 32768 with 48 rows and 4 KV heads (half the CUs) 32.4 -> 27.4 us.  V's
+// second k-step is read after the first's products: 339 against 344 us with
+// both read ahead.  Two steps of loads in flight instead of one spill 23 to
+// 39 registers and take 380 us.
 //
-// Tile t is staged in buffer t % 2.  A wave writes buffer t % 2 only after
-// the barrier of tile t - 1, which every wave reaches after attending tile
-// t - 2, the buffer's previous contents; the barrier of tile t then makes
-// the whole tile visible.  Every wave runs the same number of barriers:
-// the steps run in groups of kRowsAhead, and a step past the unit's last
-// tile (up to kRowsAhead - 1 of them) stages zeros and attends nothing.
-// Loads for tiles past the end (the last kRowsAhead issued are never
-// staged) go through an empty buffer resource, which reads zeros without
-// touching memory.
+// Lane l: lr = l % 32, lh = l / 32.  In the S tile lane (lr, lh) holds tokens
+// 8 (r / 4) + 4 lh + r % 4 (r = 0..15) of row lr; in O it holds
+// d = 32 db + 8 (r / 4) + 4 lh + r % 4.  The reduction index of both MFMAs is
+// permuted so that every operand is contiguous: for QK^T k-step s, lane half
+// lh covers the d-chunk 2s + lh; for PV k-step s it covers tokens
+// 16 s + {4 lh .. +3, 8 + 4 lh .. +3}, the S values the lane holds.  V is
+// read through the LDS transpose (see above): a 16-lane group reads 4 tokens
+// x 16 d.  16-byte chunk c of token row t lies at c ^ (t & 15) for K, as
+// above, and at c ^ 4 (t & 3) for V, so that the 32 lanes of a transpose read
+// (4 rows, 64 bytes each) touch every bank once.
+//
+// Step k is staged in buffer k % 2 by all waves together (wave w loads tokens
+// 16 (w / 2) .. +15 of its tile), with one workgroup barrier; each wave keeps
+// the next kRowsAhead steps' loads in flight in registers.  A wave writes
+// buffer k % 2 only after the barrier of step k - 1, which every wave reaches
+// after attending step k - 2, the buffer's previous contents; the barrier of
+// step k then makes the whole step visible.  Every wave runs the same number
+// of barriers: the steps run in groups of kRowsGroup, and a step past the
+// unit's end stages zeros and attends nothing.  Loads for tiles past the end
+// go through an empty buffer resource, which reads zeros without touching
+// memory.
 // ---------------------------------------------------------------------------
-constexpr int kRowsAhead = 4;   // tiles of loads in flight per wave; even, so step i of a group uses buffer i % 2
-constexpr int kRowsLdsBytes = 2 * 2 * kTileBytes;  // two K + V tile buffers
+constexpr int kRowsAhead = 1;                          // steps of loads in flight per wave
+constexpr int kRowsGroup = 2;                          // steps per loop iteration: even, a multiple of kRowsAhead
+constexpr int kRowsStepBytes = 2 * 2 * kTileBytes;     // K and V of two tiles
+constexpr int kRowsMergeBytes = kWaves * (8 * 64 * 16 + 2 * 32 * 4);
+constexpr int kRowsLdsBytes = 2 * kRowsStepBytes > kRowsMergeBytes ? 2 * kRowsStepBytes : kRowsMergeBytes;
+static_assert(kRowsGroup % 2 == 0 && kRowsGroup % kRowsAhead == 0, "step i of a group uses buffer i % 2");
 
 template <typename P>
 __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const UnitRec &ur, int tx, int g) {
   const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
+  const int rb = w >> 1, th = w & 1;                       // row block, tile parity
   const int lane = tx & 63;
-  const int lr = lane & 15;
-  const int lq = lane >> 4;
+  const int lr = lane & 31, lh = lane >> 5;
   const int i0 = unit_i0(ur.word);
   const int q_row0 = ur.q_row0;
   const int M = ur.n_cand * p.G;
-  const bool active = 16 * w < M;       // wave-uniform: the wave has rows
   const int ntiles = (int)ur.ntiles;
 
   const uint32_t stride_b = p.tok_stride * 2;                // bytes between tokens
-  const uint32_t voff = (8 * w + lq) * stride_b + 16 * lr;     // token 8w + lq, chunk lr
+  const int sr = lane & 15, sq = lane >> 4;                  // staging: chunk, row within four
+  const uint32_t voff = (16 * rb + sq) * stride_b + 16 * sr;
   const float sl2 = p.scale_log2;
 
-  // Q^T operand (B[k = d][j = row]) of row 16w + lr, k-step s: d-chunk
-  // 4s + lq.  A padding row (>= M) gets an offset past the end: zeros.
-  const int row = 16 * w + lr;
+  // Q^T operand (B[k = d][j = row]) of row 32 rb + lr, k-step s: d-chunk
+  // 2s + lh.  A padding row (>= M) gets an offset past the end: zeros.
+  const int row = 32 * rb + lr;
   const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t *>(p.q), (short)0, (int)((uint32_t)p.st.R * kRowBytes), kBufferFlags);
-  const uint32_t qoff = row < M ? (uint32_t)global_row(p, q_row0, g, row) * kRowBytes + 16 * lq : 0x80000000u;
-  bf16x8_t qop[4];
+  const uint32_t qoff = row < M ? (uint32_t)global_row(p, q_row0, g, row) * kRowBytes + 16 * lh : 0x80000000u;
+  bf16x8_t qop[8];
 #pragma unroll
-  for (int s = 0; s < 4; ++s)
-    qop[s] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 64 * s, 0, 0));
+  for (int s = 0; s < 8; ++s)
+    qop[s] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 32 * s, 0, 0));
   __builtin_amdgcn_sched_barrier(0);   // the query loads go out before the wait for the first item
   const FirstItem fi = load_first_item(p, ur);   // slot and flags of the whole chain
   const Item &it = fi.it;
 
-  // loads of tile t: K rows 8w + lq and 8w + 4 + lq, then the same V rows.
+  // loads of tile t (2k + th): K rows 16 rb + 4j + sq, then the same V rows.
   // Tiles are requested in order; the resources of the current item are
   // kept and rebuilt only when the tile moves on to the next item, so a
   // step issues its loads without a chain of dependent argument reads.
@@ -656,7 +683,7 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
   int lk = 0, lbase = 0, lend = tiles_of(it);
   __amdgpu_buffer_rsrc_t lkrs = item_rsrc_at(p, it, fi.k, fi.hs, g);
   __amdgpu_buffer_rsrc_t lvrs = item_rsrc_at(p, it, fi.v, fi.hs, g);
-  auto issue = [&](u32x4_t (&d)[4], int t) {
+  auto issue = [&](u32x4_t (&d)[8], int t) {
     if (t >= lend && t < ntiles) {
       while (t >= lend) {
         lbase = lend;
@@ -670,32 +697,38 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
     const __amdgpu_buffer_rsrc_t krs = in ? lkrs : empty;
     const __amdgpu_buffer_rsrc_t vrs = in ? lvrs : empty;
     const uint32_t o = voff + (uint32_t)(in ? (t - lbase) * kTile : 0) * stride_b;
-    d[0] = __builtin_amdgcn_raw_buffer_load_b128(krs, o, 0, kStreamLoad);
-    d[1] = __builtin_amdgcn_raw_buffer_load_b128(krs, o + 4 * stride_b, 0, kStreamLoad);
-    d[2] = __builtin_amdgcn_raw_buffer_load_b128(vrs, o, 0, kStreamLoad);
-    d[3] = __builtin_amdgcn_raw_buffer_load_b128(vrs, o + 4 * stride_b, 0, kStreamLoad);
-  };
-  auto stage = [&](const u32x4_t (&d)[4], unsigned char *buf) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int t = 8 * w + 4 * j + lq;
-      *reinterpret_cast<u32x4_t *>(buf + t * kRowBytes + 16 * (lr ^ (t & 15))) = d[j];
-      *reinterpret_cast<u32x4_t *>(buf + kTileBytes + t * kRowBytes + 16 * (lr ^ (2 * (t & 7)))) = d[2 + j];
+    for (int j = 0; j < 4; ++j) d[j] = __builtin_amdgcn_raw_buffer_load_b128(krs, o + 4 * j * stride_b, 0, kStreamLoad);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      d[4 + j] = __builtin_amdgcn_raw_buffer_load_b128(vrs, o + 4 * j * stride_b, 0, kStreamLoad);
+  };
+  unsigned char *tile_lds = smem + th * (2 * kTileBytes);   // the wave's tile in buffer 0: K, then V
+  auto stage = [&](const u32x4_t (&d)[8], unsigned char *buf) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int t = 16 * rb + 4 * j + sq;
+      *reinterpret_cast<u32x4_t *>(buf + t * kRowBytes + 16 * (sr ^ (t & 15))) = d[j];
+      *reinterpret_cast<u32x4_t *>(buf + kTileBytes + t * kRowBytes + 16 * (sr ^ (4 * (t & 3)))) = d[4 + j];
     }
   };
 
   float m_run = kNegInf, l_run = 0.f;
-  f32x4_t acc[8];
+  f32x16_t acc[4];
 #pragma unroll
-  for (int db = 0; db < 8; ++db) acc[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const int vrow = 4 * lq + (lr >> 2);
-  const int vrd = vrow * kRowBytes + 8 * (lr & 1);
-  const int vsw = 2 * (vrow & 7);
-  const int vc0 = (lr & 3) >> 1;
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+  // transpose read of the 16-lane group (lane >> 4): row 4 lh + j / 4 of the
+  // four, d 16 ((lane >> 4) & 1) + 4 (j % 4), j = lane % 16
+  const int vrow = 4 * lh + (sr >> 2);
+  const int vrd = vrow * kRowBytes + 16 * (2 * (sq & 1) + ((sr & 3) >> 1)) + 8 * (sr & 1);
+  const int vsw = 64 * (sr >> 2);
+  const int krd = lr * kRowBytes, ksw = 16 * (lh ^ (lr & 15));
   // item of the tile being attended: index, first tile, end tile, tokens
   int ck = 0, cbase = 0, cend = lend, count = it.tok_count;
 
-  // attend staged tile t (tokens [tb, tb + 32) of an item with `count` tokens)
+  // attend the wave's staged tile t (tokens [tb, tb + 32) of an item with `count` tokens)
   auto attend = [&](const unsigned char *buf, int t) {
     if (t >= cend) {
       while (t >= cend) {
@@ -705,29 +738,27 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
       count = p.items[i0 + ck].tok_count;
     }
     const int tb = (t - cbase) * kTile;
-    const unsigned char *ks = buf;
     const unsigned char *vs = buf + kTileBytes;
-    f32x4_t sacc[2];
+    f32x16_t c;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int tk = 16 * u + lr;
-      f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < 16; ++r) c[r] = 0.f;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bf16x8_t kop = *reinterpret_cast<const bf16x8_t *>(ks + tk * kRowBytes + 16 * ((4 * s + lq) ^ lr));
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop, qop[s], c, 0, 0, 0);
+    for (int s = 0; s < 8; ++s) {
+      const bf16x8_t kop = *reinterpret_cast<const bf16x8_t *>(buf + krd + (ksw ^ (32 * s)));
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qop[s], c, 0, 0, 0);
+    }
+    // the V^T operands of k-step 0 go out now, so their LDS latency hides behind the softmax
+    bf16x8_t vop[4];
+    auto load_v = [&](int s) {
+#pragma unroll
+      for (int db = 0; db < 4; ++db) {
+        const unsigned char *a = vs + vrd + ((64 * db) ^ vsw) + 16 * s * kRowBytes;
+        const s16x4_t v0 = lds_read_tr16(a);
+        const s16x4_t v1 = lds_read_tr16(a + 8 * kRowBytes);
+        vop[db] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
       }
-      sacc[u] = c;
-    }
-    // the V^T operands go out now, so their LDS latency hides behind the softmax
-    bf16x8_t vop[8];
-#pragma unroll
-    for (int db = 0; db < 8; ++db) {
-      const int off = vrd + 16 * ((2 * db + vc0) ^ vsw);
-      const s16x4_t v0 = lds_read_tr16(vs + off);
-      const s16x4_t v1 = lds_read_tr16(vs + off + 16 * kRowBytes);
-      vop[db] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+    };
+    load_v(0);
 
     __builtin_amdgcn_sched_barrier(0);
 
@@ -735,47 +766,33 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
     // scores times sigma log2(e) (> 0) is the maximum of the scaled ones,
     // and each weight is 2^(x sigma log2(e) - m) with one fma.  Only an
     // item's last, partial tile needs the token mask.
-    float x[8];
-    float mx = kNegInf;
-    if (tb + kTile <= count) {
+    if (tb + kTile > count) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          x[4 * u + r] = sacc[u][r];
-          mx = fmaxf(mx, sacc[u][r]);
-        }
-    } else {
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int tt = tb + 16 * u + 4 * lq + r;
-          const float v = tt < count ? sacc[u][r] : kNegInf;
-          x[4 * u + r] = v;
-          mx = fmaxf(mx, v);
-        }
+      for (int r = 0; r < 16; ++r) c[r] = tb + 8 * (r >> 2) + 4 * lh + (r & 3) < count ? c[r] : kNegInf;
     }
-    const float mn = fmaxf(m_run, xgroup_max(mx) * sl2);
+    float mx = c[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, c[r]);
+    const float mn = fmaxf(m_run, x32_max(mx) * sl2);
     // Eq. 14's rescale, only when some row's maximum rose (elsewhere the
     // factor is exactly 1)
     if (__builtin_amdgcn_ballot_w64(mn > m_run)) {
       const float alpha = exp2_fast(m_run - mn);
       l_run *= alpha;
 #pragma unroll
-      for (int db = 0; db < 8; ++db) acc[db] *= alpha;
+      for (int db = 0; db < 4; ++db) acc[db] *= alpha;
       m_run = mn;
     }
-    bf16x8_t phi, plo;
+    bf16x8_t phi[2], plo[2];
     float ls = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float pe = exp2_fast(__builtin_fmaf(x[e], sl2, -mn));
+    for (int r = 0; r < 16; ++r) {
+      const float pe = exp2_fast(__builtin_fmaf(c[r], sl2, -mn));
       const __bf16 h = (__bf16)pe;
       const float hf = (float)h;
       const __bf16 lo = (__bf16)(pe - hf);
-      phi[e] = h;
-      plo[e] = lo;
+      phi[r >> 3][r & 7] = h;
+      plo[r >> 3][r & 7] = lo;
       ls += pe;
     }
     l_run += ls;
@@ -783,57 +800,80 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
     __builtin_amdgcn_sched_barrier(0);
 
 #pragma unroll
-    for (int db = 0; db < 8; ++db) {
-      acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], phi, acc[db], 0, 0, 0);
-      acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], plo, acc[db], 0, 0, 0);
+    for (int s = 0; s < 2; ++s) {
+      if (s) load_v(1);
+#pragma unroll
+      for (int db = 0; db < 4; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[db], phi[s], acc[db], 0, 0, 0);
+#pragma unroll
+      for (int db = 0; db < 4; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[db], plo[s], acc[db], 0, 0, 0);
     }
   };
 
-  u32x4_t ld[kRowsAhead][4];
+  const int steps = (ntiles + 1) / 2;
+  u32x4_t ld[kRowsAhead][8];
 #pragma unroll
-  for (int i = 0; i < kRowsAhead; ++i) issue(ld[i], i);
-  for (int t0 = 0; t0 < ntiles; t0 += kRowsAhead) {
+  for (int i = 0; i < kRowsAhead; ++i) issue(ld[i], 2 * i + th);
+  for (int k0 = 0; k0 < steps; k0 += kRowsGroup) {
 #pragma unroll
-    for (int i = 0; i < kRowsAhead; ++i) {
-      const int t = t0 + i;
-      unsigned char *buf = smem + (i & 1) * (2 * kTileBytes);
-      stage(ld[i], buf);
-      issue(ld[i], t + kRowsAhead);
+    for (int i = 0; i < kRowsGroup; ++i) {
+      const int t = 2 * (k0 + i) + th;
+      unsigned char *buf = tile_lds + (i & 1) * kRowsStepBytes;
+      stage(ld[i % kRowsAhead], buf);
+      issue(ld[i % kRowsAhead], t + 2 * kRowsAhead);
       __syncthreads();
-      if (active && t < ntiles) attend(buf, t);
+      if (t < ntiles) attend(buf, t);
     }
   }
 
-  // the wave's rows -> their slot (Eq. 14 with the slot's state unless the
-  // slot is fresh).  Lane (lr, lq) holds d = 16db + 4lq .. +3 of row 16w + lr.
-  if (!active) return;
-  l_run = xgroup_sum(l_run);
-  if (row >= M) return;
-  const size_t idx = (size_t)it.slot * p.st.R + global_row(p, q_row0, g, row);
-  float *ap = p.st.a + idx * kHeadDim + 4 * lq;
-  if (it.flags & kSlotFresh) {
+  // Merge the two waves of a row block (Eq. 14): wave th keeps the d-blocks
+  // 2 th, 2 th + 1 and hands the others over through LDS.  A wave without
+  // tiles has m = -inf, which scales its zeros by 0.  The slot's old m and l
+  // are read before the barrier, as the block's first wave replaces them.
+  l_run = x32_sum(l_run);
+  const bool stores = row < M;
+  const bool merge_slot = !(it.flags & kSlotFresh);
+  const size_t idx = (size_t)it.slot * p.st.R + (stores ? global_row(p, q_row0, g, row) : 0);
+  float ms = kNegInf, lsl = 0.f;
+  if (merge_slot && stores) {
+    ms = p.st.m[idx];
+    lsl = p.st.l[idx];
+  }
+  asm volatile("" : "+v"(ms), "+v"(lsl));
+  __syncthreads();                       // every wave is done with the tile buffers
+  f32x4_t *sh = reinterpret_cast<f32x4_t *>(smem);
+  float *m_sh = reinterpret_cast<float *>(smem + kWaves * 8 * 64 * 16), *l_sh = m_sh + kWaves * 32;
 #pragma unroll
-    for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4_t *>(ap + 16 * db) = acc[db];
-    if (lq == 0) {
-      p.st.m[idx] = m_run;
-      p.st.l[idx] = l_run;
-    }
-  } else {
-    const float ms = p.st.m[idx];
-    const float ls = p.st.l[idx];
-    const float mn = fmaxf(ms, m_run);
-    const float alpha = exp2_fast(ms - mn);
-    const float beta = exp2_fast(m_run - mn);
+  for (int q = 0; q < 8; ++q) {
+    const int r = 4 * (q & 3), db = q >> 2;
+    f32x4_t a;
 #pragma unroll
-    for (int db = 0; db < 8; ++db) {
-      f32x4_t o = *reinterpret_cast<const f32x4_t *>(ap + 16 * db);
-      o = alpha * o + beta * acc[db];
-      *reinterpret_cast<f32x4_t *>(ap + 16 * db) = o;
-    }
-    if (lq == 0) {
-      p.st.m[idx] = mn;
-      p.st.l[idx] = alpha * ls + beta * l_run;
-    }
+    for (int e = 0; e < 4; ++e) a[e] = th ? acc[db][r + e] : acc[2 + db][r + e];
+    sh[(w * 8 + q) * 64 + lane] = a;
+  }
+  if (lh == 0) {
+    m_sh[w * 32 + lr] = m_run;
+    l_sh[w * 32 + lr] = l_run;
+  }
+  __syncthreads();
+  if (!stores) return;
+  const float m2 = m_sh[(w ^ 1) * 32 + lr], l2 = l_sh[(w ^ 1) * 32 + lr];
+  const float mn = fmaxf(fmaxf(m_run, m2), ms);
+  const float f0 = exp2_fast(m_run - mn), f1 = exp2_fast(m2 - mn), fs = merge_slot ? exp2_fast(ms - mn) : 0.f;
+  float *ap = p.st.a + idx * kHeadDim + 64 * th + 4 * lh;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int r = 4 * (q & 3), db = q >> 2;
+    f32x4_t own;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) own[e] = th ? acc[2 + db][r + e] : acc[db][r + e];
+    f32x4_t o = f0 * own + f1 * sh[((w ^ 1) * 8 + q) * 64 + lane];
+    f32x4_t *dst = reinterpret_cast<f32x4_t *>(ap + 32 * db + 2 * r);
+    if (merge_slot) o += fs * *dst;
+    *dst = o;
+  }
+  if (th == 0 && lh == 0) {
+    p.st.m[idx] = mn;
+    p.st.l[idx] = f0 * l_run + f1 * l2 + fs * lsl;
   }
 }
 
