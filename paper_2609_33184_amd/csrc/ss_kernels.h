@@ -63,11 +63,9 @@ struct State {
   int32_t R;        // rows = sum n_b * Hq
 };
 
-// Kernel arguments.  The unit and item tables travel by value in the
-// kernel-argument segment; the launch wrappers pick the smallest of three
-// table capacities that holds a launch, so a typical round passes a few KB
-// (large by-value arguments fill the runtime's argument pool quickly, and a
-// full pool makes the next launch wait for the queue to drain).
+// A launch as the planner fills it.  The unit and item tables travel by value
+// in the kernel-argument segment; the launch wrappers put them into the form
+// the kernels read and pick the smallest table class that holds a launch.
 struct ChunkHeader {
   const uint16_t *q;    // bf16 [sum n_b, Hq, d]
   State st;
@@ -97,12 +95,9 @@ struct ChunkHeader {
   int32_t num_tail;
 };
 
-// Unit record: what a workgroup needs to start a unit, so that its first
-// loads depend on one record and the item and chunk-table entries it names
-// (kernel arguments are read with dependent loads of about a microsecond
-// each at the start of a launch).  word packs the unit's first item i0
-// (within the launch), its item count nit (1..kMaxChain; 0 = no unit), the
-// body kind and the chunk of item i0; ntiles is the chain's tile count.
+// Unit record.  word packs the unit's first item i0 (within the launch), its
+// item count nit (1..kMaxChain; 0 = no unit), the body kind and the chunk of
+// item i0; ntiles is the chain's tile count.
 struct UnitRec {
   uint32_t word;
   uint32_t ntiles;

@@ -40,6 +40,7 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 // Global memory reached through a pointer whose origin the compiler cannot see.
 typedef __attribute__((address_space(1))) float GlobalFloat;
 typedef __attribute__((address_space(1))) f32x4_t GlobalFloat4;
+typedef __attribute__((address_space(1))) u32x4_t GlobalU32x4;
 
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr int kAwPitch = 132;  // floats per row of a wave's partial accumulator
@@ -106,12 +107,47 @@ __device__ __forceinline__ float x32_max(float x) {
 __device__ __forceinline__ float xgroup_max(float x) { return x32_max(x16_max(x)); }
 __device__ __forceinline__ float xgroup_sum(float x) { return x32_sum(x16_sum(x)); }
 
-template <typename P>
-__device__ __forceinline__ int global_row(const P &p, int q_row0, int g, int r) {
+// Kernel-argument form of a unit: all that its first loads need, so that they
+// wait for one scalar round trip (0.36 us after a workgroup's start).  With the
+// item, the chunk table and the header behind one another a workgroup's first
+// K/V load went out 0.4 us later.  k, v point at the first item's first token
+// of KV head 0.  Rounds back to back, before and after: 1 x 16384 tokens 19.4 ->
+// 18.3 us, 24 ragged short requests 26.6 -> 25.5 us, 16 x 32768 tokens by chunk
+// (8 launches) 386.5 -> 382.9 us, in one call 308.6 -> 307.5 us, 32 x 131072
+// tokens 2395 -> 2391 us (with tables of 42 KB for the last, 2399 us).
+struct UnitArg {
+  const uint16_t *k, *v;
+  uint64_t hs;           // elements between KV heads
+  uint32_t word;         // see UnitRec
+  uint32_t ntiles;
+  int32_t tok_count;     // of the first item
+  int32_t q_row0;
+  uint32_t cand_slot;    // n_cand | slot << 8 | flags << 16
+  uint32_t pad;
+};
+static_assert(sizeof(UnitArg) == 48, "UnitArg layout");
+__host__ __device__ __forceinline__ uint32_t pack_cand_slot(const Item &it) {
+  return (uint32_t)it.n_cand | (uint32_t)it.slot << 8 | (uint32_t)it.flags << 16;
+}
+__device__ __forceinline__ int unit_cand(const UnitArg &u) { return (int)(u.cand_slot & 0xffu); }
+__device__ __forceinline__ uint32_t unit_slot(const UnitArg &u) { return (u.cand_slot >> 8) & 0xffu; }
+__device__ __forceinline__ bool unit_fresh(const UnitArg &u) { return (u.cand_slot >> 16) & kSlotFresh; }
+
+// What every unit of a launch needs of its arguments, read once at the start.
+struct Ctx {
+  const uint16_t *q;
+  GlobalFloat *a, *m, *l;   // the state's arrays
+  uint32_t R;               // query rows
+  int Hq, G;
+  uint32_t g_inv;           // ceil(65536 / G): r / G = r * g_inv >> 16 for r < 64, G <= 64
+  float sl2;                // sigma log2(e)
+  uint32_t stride_b;        // bytes between consecutive tokens of a KV head
+};
+
+__device__ __forceinline__ int global_row(const Ctx &c, int q_row0, int g, int r) {
   // local row r of (request, kv head g) -> packed query row (off_b + i) * Hq + h
-  const int i = r / p.G;
-  const int h = g * p.G + (r - i * p.G);
-  return (q_row0 + i) * p.Hq + h;
+  const int i = (int)(((uint32_t)r * c.g_inv) >> 16);
+  return (q_row0 + i) * c.Hq + g * c.G + (r - i * c.G);
 }
 
 // ---------------------------------------------------------------------------
@@ -120,14 +156,15 @@ __device__ __forceinline__ int global_row(const P &p, int q_row0, int g, int r) 
 // all relative to their own maxima); combine them (Eq. 14 over the waves) and
 // fold the result into the item's slot of the running state (Eq. 14 again).
 // ---------------------------------------------------------------------------
-template <int ROWS, typename P>
-__device__ __forceinline__ void fold_into_slot(const P &p, const Item &it, int q_row0, int g, int M, int tx,
-                                               const float *aw, const float *mw, const float *lw) {
+template <int ROWS>
+__device__ __forceinline__ void fold_into_slot(const Ctx &c, const UnitArg &u, int g, int M, int tx, const float *aw,
+                                               const float *mw, const float *lw) {
   // SEGS threads per row (the largest power of two with SEGS * ROWS <= 256,
-  // at most 32), SEGLEN (a multiple of 4) values each
+  // at most 32); thread seg takes the row's 16-byte pieces seg, seg + SEGS, ...,
+  // so that a row's threads read and write neighbouring pieces
   constexpr int SEGS = (256 / ROWS) >= 32 ? 32 : (256 / ROWS) >= 16 ? 16 : (256 / ROWS) >= 8 ? 8 : 4;
-  constexpr int SEGLEN = kHeadDim / SEGS;
-  static_assert(SEGLEN % 4 == 0 && SEGS * ROWS <= 256, "fold layout");
+  constexpr int PIECES = kHeadDim / 4 / SEGS;
+  static_assert(PIECES >= 1 && SEGS * ROWS <= 256, "fold layout");
   const int r = tx / SEGS;
   const int seg = tx % SEGS;
   if (r >= M) return;
@@ -145,48 +182,37 @@ __device__ __forceinline__ void fold_into_slot(const P &p, const Item &it, int q
     f[w] = exp2_fast(mwv[w] - mstar);   // a wave without tokens has m = -inf -> 0
     lstar += f[w] * lw[w * ROWS + r];
   }
-  float a[SEGLEN];
+  f32x4_t a[PIECES];
 #pragma unroll
-  for (int c = 0; c < SEGLEN; ++c) a[c] = 0.f;
+  for (int k = 0; k < PIECES; ++k) a[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    const float *src = aw + (w * ROWS + r) * kAwPitch + seg * SEGLEN;
+    const float *src = aw + (w * ROWS + r) * kAwPitch + 4 * seg;
 #pragma unroll
-    for (int c = 0; c < SEGLEN; c += 4) {
-      const f32x4_t x = *reinterpret_cast<const f32x4_t *>(src + c);
-      a[c] += f[w] * x[0];
-      a[c + 1] += f[w] * x[1];
-      a[c + 2] += f[w] * x[2];
-      a[c + 3] += f[w] * x[3];
-    }
+    for (int k = 0; k < PIECES; ++k) a[k] += f[w] * *reinterpret_cast<const f32x4_t *>(src + 4 * SEGS * k);
   }
-  const size_t idx = (size_t)it.slot * p.st.R + global_row(p, q_row0, g, r);
-  float *ap = p.st.a + idx * kHeadDim + seg * SEGLEN;
-  if (it.flags & kSlotFresh) {       // first write of this slot in the round: store
+  const size_t idx = (size_t)unit_slot(u) * c.R + global_row(c, u.q_row0, g, r);
+  GlobalFloat *ap = c.a + idx * kHeadDim + 4 * seg;
+  if (unit_fresh(u)) {               // first write of this slot in the round: store
 #pragma unroll
-    for (int c = 0; c < SEGLEN; c += 4)
-      *reinterpret_cast<f32x4_t *>(ap + c) = f32x4_t{a[c], a[c + 1], a[c + 2], a[c + 3]};
+    for (int k = 0; k < PIECES; ++k) *(GlobalFloat4 *)(ap + 4 * SEGS * k) = a[k];
     if (seg == 0) {
-      p.st.m[idx] = mstar;
-      p.st.l[idx] = lstar;
+      c.m[idx] = mstar;
+      c.l[idx] = lstar;
     }
   } else {
-    const float ms = p.st.m[idx];
+    const float ms = c.m[idx];
     const float mn = fmaxf(ms, mstar);
     const float alpha = exp2_fast(ms - mn);
     const float beta = exp2_fast(mstar - mn);
 #pragma unroll
-    for (int c = 0; c < SEGLEN; c += 4) {
-      f32x4_t o = *reinterpret_cast<const f32x4_t *>(ap + c);
-      o[0] = alpha * o[0] + beta * a[c];
-      o[1] = alpha * o[1] + beta * a[c + 1];
-      o[2] = alpha * o[2] + beta * a[c + 2];
-      o[3] = alpha * o[3] + beta * a[c + 3];
-      *reinterpret_cast<f32x4_t *>(ap + c) = o;
+    for (int k = 0; k < PIECES; ++k) {
+      GlobalFloat4 *o = (GlobalFloat4 *)(ap + 4 * SEGS * k);
+      *o = alpha * *o + beta * a[k];
     }
     if (seg == 0) {
-      p.st.m[idx] = mn;
-      p.st.l[idx] = alpha * p.st.l[idx] + beta * lstar;
+      c.m[idx] = mn;
+      c.l[idx] = alpha * c.l[idx] + beta * lstar;
     }
   }
 }
@@ -231,75 +257,95 @@ __device__ __forceinline__ void fold_into_slot(const P &p, const Item &it, int q
 constexpr int kRowBytes = kHeadDim * 2;          // 256
 constexpr int kTileBytes = kTile * kRowBytes;    // 8 KiB per K or V tile
 
-__device__ __forceinline__ int tiles_of(const Item &it) { return (it.tok_count + kTile - 1) / kTile; }
+__device__ __forceinline__ int tiles_of(int tokens) { return (tokens + kTile - 1) / kTile; }
 
-// Chunk-table index of an item.  The item is read as whole dwords: a
-// byte-sized read of a kernel argument becomes a vector memory load, and the
-// wait for it would also wait for every K/V load in flight.
-__device__ __forceinline__ int item_chunk(const Item &it) {
-  uint32_t w[4];
-  __builtin_memcpy(w, &it, sizeof w);
-  return (int)((w[3] >> 8) & 0xffu);
-}
-static_assert(offsetof(Item, chunk) == 13, "Item layout");
-
-// Buffer resource over item `it`'s rows of KV head g in the chunk that
-// starts at `base` (K or V) with head_stride `hs` elements: loads past the
-// item's last token return zero, so no clamping is needed.  Offsets are
-// 32-bit (the host keeps an item below 2^31 bytes).
-template <typename P>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc_at(const P &p, const Item &it, const uint16_t *base,
-                                                               uint64_t hs, int g) {
-  const uint32_t nrec = (uint32_t)(it.tok_count - 1) * (p.tok_stride * 2) + kRowBytes;
-  const size_t first = (size_t)it.tok_begin * p.tok_stride + (size_t)g * hs;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base + first), (short)0, (int)nrec, kBufferFlags);
-}
-// The same through the launch's chunk table `tab` (p.k or p.v).
-template <typename P>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const P &p, const Item &it, int chunk, int g,
-                                                            const uint16_t *const *tab) {
-  return item_rsrc_at(p, it, tab[chunk], p.head_stride[chunk], g);
+// Buffer resource over `tokens` rows from `base` on: loads past the last row
+// return zero, so no clamping is needed.  Offsets are 32-bit (the host keeps
+// an item below 2^31 bytes).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const Ctx &c, const uint16_t *base, int tokens) {
+  const uint32_t nrec = (uint32_t)(tokens - 1) * c.stride_b + kRowBytes;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), (short)0, (int)nrec, kBufferFlags);
 }
 
-// A unit's first item and its chunk-table entries.  The item is read as
-// whole dwords, and the item and the three entries are forced into
-// registers at one point, so their loads go out together (the chunk comes
-// from the unit record, not from the item) and are waited for once.
-struct FirstItem {
-  Item it;
-  const uint16_t *k, *v;
-  uint64_t hs;
+// Kernel-argument form of an item: what a chain needs past its first.
+struct ChainItem {
+  uint32_t begin;        // first token
+  uint32_t word;         // tokens (below 2^24: a 2^31-byte item of 256-byte rows at most) | chunk << 24
 };
+// An item in registers, read as whole dwords: a byte-sized read of a kernel
+// argument becomes a vector memory load, and the wait for it would also wait
+// for every K/V load in flight.
+struct ItemWords {
+  uint32_t begin, count, chunk, cand_slot;
+};
+static_assert(sizeof(Item) == 16 && offsetof(Item, n_cand) == 12 && offsetof(Item, chunk) == 13 &&
+              offsetof(Item, slot) == 14 && offsetof(Item, flags) == 15, "Item layout");
 template <typename P>
-__device__ __forceinline__ FirstItem load_first_item(const P &p, const UnitRec &ur) {
-  const int i0 = unit_i0(ur.word), c = unit_chunk(ur.word);
-  uint32_t w[4];
-  __builtin_memcpy(w, &p.items[i0], sizeof w);
-  const uint16_t *k = p.k[c];
-  const uint16_t *v = p.v[c];
-  uint64_t hs = p.head_stride[c];
-  asm volatile("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]), "+s"(k), "+s"(v), "+s"(hs));
-  FirstItem f;
-  __builtin_memcpy(&f.it, w, sizeof w);
-  f.k = k;
-  f.v = v;
-  f.hs = hs;
-  return f;
+__device__ __forceinline__ ItemWords item_at(const P &p, int i) {
+  if constexpr (P::kFat) {
+    uint32_t begin = p.items[i].begin, word = p.items[i].word;
+    asm volatile("" : "+s"(begin), "+s"(word));
+    return {begin, word & 0xffffffu, word >> 24, 0u};
+  } else {
+    uint32_t w[4];
+    __builtin_memcpy(w, &p.items[i], sizeof w);
+    asm volatile("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[3]));
+    return {w[0], w[1], (w[3] >> 8) & 0xffu, (w[3] & 0xffu) | (w[3] >> 16) << 8};
+  }
 }
 
 // A unit's tiles are numbered across its chain of items (item 0's tiles
-// first).  The cursor maps a global tile T to (item k, k's first global
-// tile); it only moves forward, and never past the chain's last item.
-struct TileCursor {
-  int k = 0;
-  int base = 0;
-};
-template <typename P>
-__device__ __forceinline__ void seek(const P &p, int i0, int nit, TileCursor &c, int T) {
-  while (c.k + 1 < nit && T - c.base >= tiles_of(p.items[i0 + c.k])) {
-    c.base += tiles_of(p.items[i0 + c.k]);
-    ++c.k;
+// first).  The cursor holds the item of the tile last asked for; it only
+// moves forward.
+struct Cursor {
+  int k, base, end;         // item, its first tile, the tile after its last
+  int count;                // its tokens
+  __device__ __forceinline__ explicit Cursor(const UnitArg &u)
+      : k(0), base(0), end(tiles_of(u.tok_count)), count(u.tok_count) {}
+  // Move to tile T (T < the unit's tiles, T >= end); the item moved to.
+  template <typename P>
+  __device__ __forceinline__ ItemWords seek(const P &p, int i0, int T) {
+    ItemWords it;
+    do {
+      it = item_at(p, i0 + ++k);
+      base = end;
+      end += tiles_of((int)it.count);
+    } while (T >= end);
+    count = (int)it.count;
+    return it;
   }
+};
+
+// Resource of item `it` of KV head g through the launch's chunk table `tab` (p.k or p.v).
+template <typename P>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t item_rsrc(const P &p, const Ctx &c, const ItemWords &it, int g,
+                                                            const uint16_t *const *tab) {
+  const size_t first = (size_t)it.begin * (c.stride_b / 2) + (size_t)g * p.head_stride[it.chunk];
+  return rows_rsrc(c, tab[it.chunk] + first, (int)it.count);
+}
+
+// Unit u's argument record.  Launches of the largest table class hold units as
+// UnitRec and gather the rest here, behind a second round trip.
+template <typename P>
+__device__ __forceinline__ UnitArg unit_at(const P &p, uint32_t u) {
+  UnitArg a;
+  if constexpr (P::kFat) {
+    a = p.units[u];
+  } else {
+    const UnitRec r = p.units[u];
+    const int c = unit_chunk(r.word);
+    const ItemWords it = item_at(p, unit_i0(r.word));
+    const size_t first = (size_t)it.begin * p.tok_stride;
+    a.k = p.k[c] + first;
+    a.v = p.v[c] + first;
+    a.hs = p.head_stride[c];
+    a.word = r.word;
+    a.ntiles = r.ntiles;
+    a.tok_count = (int)it.count;
+    a.q_row0 = r.q_row0;
+    a.cand_slot = it.cand_slot;
+  }
+  return a;
 }
 
 // Resources and item-local token base of the next tile a wave loads.
@@ -324,15 +370,15 @@ __device__ __forceinline__ s16x4_t lds_read_tr16(const unsigned char *p) {
 }
 
 template <int RB, typename P>
-__device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const UnitRec &ur, int tx, int g, int nxt) {
+__device__ __forceinline__ void mfma_unit(const P &p, const Ctx &c, unsigned char *smem, const UnitArg &ua, int tx, int g,
+                                          int nxt) {
   const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
   const int lane = tx & 63;
   const int lr = lane & 15;
   const int lq = lane >> 4;
-  const int i0 = unit_i0(ur.word), nit = unit_nit(ur.word);
-  const int q_row0 = ur.q_row0;
-  const int M = ur.n_cand * p.G;
-  const int ntiles = (int)ur.ntiles;
+  const int i0 = unit_i0(ua.word);
+  const int M = unit_cand(ua) * c.G;
+  const int ntiles = (int)ua.ntiles;
 
   float m_run[RB], l_run[RB];
   f32x4_t acc[RB][8];
@@ -344,12 +390,12 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
     for (int db = 0; db < 8; ++db) acc[rb][db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
-  const uint32_t stride_b = p.tok_stride * 2;                      // bytes between tokens
+  const uint32_t stride_b = c.stride_b;
   const uint32_t voff = lq * stride_b + 16 * lr;                     // token lq, chunk lr
   unsigned char *qs = smem;
   unsigned char *ks = smem + MfmaLds<RB>::kQBytes + w * (2 * kTileBytes);
   unsigned char *vs = ks + kTileBytes;
-  const float sl2 = p.scale_log2;
+  const float sl2 = c.sl2;
 
   u32x4_t kr[8], vr[8];
   // coalesced loads: instruction i reads tokens tb + 4i + lq, chunk lr.  The
@@ -396,14 +442,14 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
         kop[s] = *reinterpret_cast<const bf16x8_t *>(ks + t * kRowBytes + 16 * ((4 * s + lq) ^ lr));
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+        f32x4_t x = {0.f, 0.f, 0.f, 0.f};
         const unsigned char *qrow = qs + (16 * rb + lr) * kRowBytes;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const bf16x8_t qop = *reinterpret_cast<const bf16x8_t *>(qrow + 16 * ((4 * s + lq) ^ lr));
-          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[s], qop, c, 0, 0, 0);
+          x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[s], qop, x, 0, 0, 0);
         }
-        sacc[u][rb] = c;
+        sacc[u][rb] = x;
       }
     }
 
@@ -487,74 +533,61 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
   // branch (whose merge with the zero default would force an early wait).
   constexpr int kQPerThread = RB * 16 * 16 / 256;
   const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t *>(p.q), (short)0, (int)((uint32_t)p.st.R * kRowBytes), kBufferFlags);
+      const_cast<uint16_t *>(c.q), (short)0, (int)(c.R * kRowBytes), kBufferFlags);
   u32x4_t qv[kQPerThread];
 #pragma unroll
   for (int e = 0; e < kQPerThread; ++e) {
-    const int c = tx + 256 * e, r = c >> 4, ch = c & 15;
-    const uint32_t qoff = r < M ? (uint32_t)global_row(p, q_row0, g, r) * kRowBytes + 16 * ch : 0x80000000u;
+    const int ci = tx + 256 * e, r = ci >> 4, ch = ci & 15;
+    const uint32_t qoff = r < M ? (uint32_t)global_row(c, ua.q_row0, g, r) * kRowBytes + 16 * ch : 0x80000000u;
     qv[e] = __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff, 0, 0);
   }
-  __builtin_amdgcn_sched_barrier(0);   // the query loads go out before the wait for the first item
   // wave w takes the chain's tiles T = w, w + 4, ...  The first tile's loads
   // are issued unconditionally (a wave without tiles loads through an empty
   // resource, which reads nothing), so the wait for the query rows below
-  // does not have to include them.  The first item (slot and flags of the
-  // whole chain) comes with its chunk; a wave whose first tile lies in a
-  // later item of the chain rebuilds its resources from that item.
-  const FirstItem fi = load_first_item(p, ur);
-  const Item &it = fi.it;
+  // does not have to include them.  A wave whose first tile lies in a later
+  // item of the chain rebuilds its resources from that item.
+  int T = w;
+  Cursor cur(ua);
+  NextTile nx;
+  const __amdgpu_buffer_rsrc_t empty =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(c.q), (short)0, 0, kBufferFlags);
+  const bool has_tile = T < ntiles;
+  nx.krs = has_tile ? rows_rsrc(c, ua.k + (size_t)g * ua.hs, ua.tok_count) : empty;
+  nx.vrs = has_tile ? rows_rsrc(c, ua.v + (size_t)g * ua.hs, ua.tok_count) : empty;
+  if (has_tile && T >= cur.end) {
+    const ItemWords ic = cur.seek(p, i0, T);
+    nx.krs = item_rsrc(p, c, ic, g, p.k);
+    nx.vrs = item_rsrc(p, c, ic, g, p.v);
+  }
+  nx.tb = (T - cur.base) * kTile;
+  __builtin_amdgcn_sched_barrier(0);   // the query loads go out first
+  load_kv(nx);
   // The workgroup's next unit of its own list (nxt >= 0): its first item's
   // resources, read now, so that each wave can bring the lines of its first
   // tile of that unit into the L2 cache during its last tile of this one.
-  __amdgpu_buffer_rsrc_t wkrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.q), (short)0, 0, kBufferFlags);
-  __amdgpu_buffer_rsrc_t wvrs = wkrs;
+  __amdgpu_buffer_rsrc_t wkrs = empty, wvrs = empty;
   if (nxt >= 0) {
-    const UnitRec un = p.units[nxt];
-    const Item in0 = p.items[unit_i0(un.word)];
-    const int cn = unit_chunk(un.word);
-    wkrs = item_rsrc(p, in0, cn, g, p.k);
-    wvrs = item_rsrc(p, in0, cn, g, p.v);
+    const UnitArg un = unit_at(p, (uint32_t)nxt);
+    wkrs = rows_rsrc(c, un.k + (size_t)g * un.hs, un.tok_count);
+    wvrs = rows_rsrc(c, un.v + (size_t)g * un.hs, un.tok_count);
   }
-  int T = w;
-  TileCursor cur;
-  NextTile nx;
-  const __amdgpu_buffer_rsrc_t empty =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.q), (short)0, 0, kBufferFlags);
-  const bool has_tile = T < ntiles;
-  nx.krs = has_tile ? item_rsrc_at(p, it, fi.k, fi.hs, g) : empty;
-  nx.vrs = has_tile ? item_rsrc_at(p, it, fi.v, fi.hs, g) : empty;
-  nx.tb = T * kTile;
-  if (has_tile && T >= tiles_of(it)) {
-    seek(p, i0, nit, cur, T);
-    const Item ic = p.items[i0 + cur.k];
-    nx.krs = item_rsrc(p, ic, item_chunk(ic), g, p.k);
-    nx.vrs = item_rsrc(p, ic, item_chunk(ic), g, p.v);
-    nx.tb = (T - cur.base) * kTile;
-  }
-  load_kv(nx);
 #pragma unroll
   for (int e = 0; e < kQPerThread; ++e) {
-    const int c = tx + 256 * e, r = c >> 4, ch = c & 15;
+    const int ci = tx + 256 * e, r = ci >> 4, ch = ci & 15;
     *reinterpret_cast<u32x4_t *>(qs + r * kRowBytes + 16 * (ch ^ (r & 15))) = qv[e];
   }
   __syncthreads();
 
   if (T < ntiles) {
-    int tb = nx.tb;
-    int count = cur.k == 0 ? it.tok_count : p.items[i0 + cur.k].tok_count;
     for (; T + kWaves < ntiles; T += kWaves) {
-      const int kprev = cur.k;
-      seek(p, i0, nit, cur, T + kWaves);
-      if (cur.k != kprev) {
-        const Item in = p.items[i0 + cur.k];
-        nx.krs = item_rsrc(p, in, item_chunk(in), g, p.k);
-        nx.vrs = item_rsrc(p, in, item_chunk(in), g, p.v);
+      const int tb = nx.tb, count = cur.count;
+      if (T + kWaves >= cur.end) {
+        const ItemWords in = cur.seek(p, i0, T + kWaves);
+        nx.krs = item_rsrc(p, c, in, g, p.k);
+        nx.vrs = item_rsrc(p, c, in, g, p.v);
       }
       nx.tb = (T + kWaves - cur.base) * kTile;
       tile(tb, count, std::integral_constant<bool, true>{}, nx);
-      tb = nx.tb;
-      count = p.items[i0 + cur.k].tok_count;
     }
     // one 4-byte read per 128-byte line of this wave's first tile of the
     // next unit (tokens 32w .. 32w+31 of its first item, K and V; reads
@@ -567,7 +600,7 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
       warm_k = __builtin_amdgcn_raw_buffer_load_b32(wkrs, wo, 0, 0);
       warm_v = __builtin_amdgcn_raw_buffer_load_b32(wvrs, wo, 0, 0);
     }
-    tile(tb, count, std::integral_constant<bool, false>{}, nx);
+    tile(nx.tb, cur.count, std::integral_constant<bool, false>{}, nx);
     asm volatile("" ::"v"(warm_k), "v"(warm_v));
   }
 
@@ -589,7 +622,7 @@ __device__ __forceinline__ void mfma_unit(const P &p, unsigned char *smem, const
     }
   }
   __syncthreads();
-  fold_into_slot<RB * 16>(p, it, q_row0, g, M, tx, aw, mw, lw);
+  fold_into_slot<RB * 16>(c, ua, g, M, tx, aw, mw, lw);
 }
 
 // ---------------------------------------------------------------------------
@@ -642,34 +675,31 @@ constexpr int kRowsLdsBytes = 2 * kRowsStepBytes > kRowsMergeBytes ? 2 * kRowsSt
 static_assert(kRowsGroup % 2 == 0 && kRowsGroup % kRowsAhead == 0, "step i of a group uses buffer i % 2");
 
 template <typename P>
-__device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const UnitRec &ur, int tx, int g) {
+__device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned char *smem, const UnitArg &ua, int tx, int g) {
   const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
   const int rb = w >> 1, th = w & 1;                       // row block, tile parity
   const int lane = tx & 63;
   const int lr = lane & 31, lh = lane >> 5;
-  const int i0 = unit_i0(ur.word);
-  const int q_row0 = ur.q_row0;
-  const int M = ur.n_cand * p.G;
-  const int ntiles = (int)ur.ntiles;
+  const int i0 = unit_i0(ua.word);
+  const int M = unit_cand(ua) * cx.G;
+  const int ntiles = (int)ua.ntiles;
 
-  const uint32_t stride_b = p.tok_stride * 2;                // bytes between tokens
+  const uint32_t stride_b = cx.stride_b;
   const int sr = lane & 15, sq = lane >> 4;                  // staging: chunk, row within four
   const uint32_t voff = (16 * rb + sq) * stride_b + 16 * sr;
-  const float sl2 = p.scale_log2;
+  const float sl2 = cx.sl2;
 
   // Q^T operand (B[k = d][j = row]) of row 32 rb + lr, k-step s: d-chunk
   // 2s + lh.  A padding row (>= M) gets an offset past the end: zeros.
   const int row = 32 * rb + lr;
   const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t *>(p.q), (short)0, (int)((uint32_t)p.st.R * kRowBytes), kBufferFlags);
-  const uint32_t qoff = row < M ? (uint32_t)global_row(p, q_row0, g, row) * kRowBytes + 16 * lh : 0x80000000u;
+      const_cast<uint16_t *>(cx.q), (short)0, (int)(cx.R * kRowBytes), kBufferFlags);
+  const uint32_t qoff = row < M ? (uint32_t)global_row(cx, ua.q_row0, g, row) * kRowBytes + 16 * lh : 0x80000000u;
   bf16x8_t qop[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s)
     qop[s] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 32 * s, 0, 0));
-  __builtin_amdgcn_sched_barrier(0);   // the query loads go out before the wait for the first item
-  const FirstItem fi = load_first_item(p, ur);   // slot and flags of the whole chain
-  const Item &it = fi.it;
+  __builtin_amdgcn_sched_barrier(0);   // the query loads go out first
 
   // loads of tile t (2k + th): K rows 16 rb + 4j + sq, then the same V rows.
   // Tiles are requested in order; the resources of the current item are
@@ -679,24 +709,20 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
   // the compiler wait for every outstanding one): past the unit's last tile
   // they go through an empty resource.
   const __amdgpu_buffer_rsrc_t empty =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.q), (short)0, 0, kBufferFlags);
-  int lk = 0, lbase = 0, lend = tiles_of(it);
-  __amdgpu_buffer_rsrc_t lkrs = item_rsrc_at(p, it, fi.k, fi.hs, g);
-  __amdgpu_buffer_rsrc_t lvrs = item_rsrc_at(p, it, fi.v, fi.hs, g);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(cx.q), (short)0, 0, kBufferFlags);
+  Cursor lcur(ua);
+  __amdgpu_buffer_rsrc_t lkrs = rows_rsrc(cx, ua.k + (size_t)g * ua.hs, ua.tok_count);
+  __amdgpu_buffer_rsrc_t lvrs = rows_rsrc(cx, ua.v + (size_t)g * ua.hs, ua.tok_count);
   auto issue = [&](u32x4_t (&d)[8], int t) {
-    if (t >= lend && t < ntiles) {
-      while (t >= lend) {
-        lbase = lend;
-        lend += tiles_of(p.items[i0 + ++lk]);
-      }
-      const Item il = p.items[i0 + lk];
-      lkrs = item_rsrc(p, il, item_chunk(il), g, p.k);
-      lvrs = item_rsrc(p, il, item_chunk(il), g, p.v);
+    if (t >= lcur.end && t < ntiles) {
+      const ItemWords il = lcur.seek(p, i0, t);
+      lkrs = item_rsrc(p, cx, il, g, p.k);
+      lvrs = item_rsrc(p, cx, il, g, p.v);
     }
     const bool in = t < ntiles;
     const __amdgpu_buffer_rsrc_t krs = in ? lkrs : empty;
     const __amdgpu_buffer_rsrc_t vrs = in ? lvrs : empty;
-    const uint32_t o = voff + (uint32_t)(in ? (t - lbase) * kTile : 0) * stride_b;
+    const uint32_t o = voff + (uint32_t)(in ? (t - lcur.base) * kTile : 0) * stride_b;
 #pragma unroll
     for (int j = 0; j < 4; ++j) d[j] = __builtin_amdgcn_raw_buffer_load_b128(krs, o + 4 * j * stride_b, 0, kStreamLoad);
 #pragma unroll
@@ -725,19 +751,12 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
   const int vrd = vrow * kRowBytes + 16 * (2 * (sq & 1) + ((sr & 3) >> 1)) + 8 * (sr & 1);
   const int vsw = 64 * (sr >> 2);
   const int krd = lr * kRowBytes, ksw = 16 * (lh ^ (lr & 15));
-  // item of the tile being attended: index, first tile, end tile, tokens
-  int ck = 0, cbase = 0, cend = lend, count = it.tok_count;
+  Cursor cur(ua);   // of the tile being attended
 
   // attend the wave's staged tile t (tokens [tb, tb + 32) of an item with `count` tokens)
   auto attend = [&](const unsigned char *buf, int t) {
-    if (t >= cend) {
-      while (t >= cend) {
-        cbase = cend;
-        cend += tiles_of(p.items[i0 + ++ck]);
-      }
-      count = p.items[i0 + ck].tok_count;
-    }
-    const int tb = (t - cbase) * kTile;
+    if (t >= cur.end) cur.seek(p, i0, t);
+    const int tb = (t - cur.base) * kTile, count = cur.count;
     const unsigned char *vs = buf + kTileBytes;
     f32x16_t c;
 #pragma unroll
@@ -831,12 +850,12 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
   // are read before the barrier, as the block's first wave replaces them.
   l_run = x32_sum(l_run);
   const bool stores = row < M;
-  const bool merge_slot = !(it.flags & kSlotFresh);
-  const size_t idx = (size_t)it.slot * p.st.R + (stores ? global_row(p, q_row0, g, row) : 0);
+  const bool merge_slot = !unit_fresh(ua);
+  const size_t idx = (size_t)unit_slot(ua) * cx.R + (stores ? global_row(cx, ua.q_row0, g, row) : 0);
   float ms = kNegInf, lsl = 0.f;
   if (merge_slot && stores) {
-    ms = p.st.m[idx];
-    lsl = p.st.l[idx];
+    ms = cx.m[idx];
+    lsl = cx.l[idx];
   }
   asm volatile("" : "+v"(ms), "+v"(lsl));
   __syncthreads();                       // every wave is done with the tile buffers
@@ -859,7 +878,7 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
   const float m2 = m_sh[(w ^ 1) * 32 + lr], l2 = l_sh[(w ^ 1) * 32 + lr];
   const float mn = fmaxf(fmaxf(m_run, m2), ms);
   const float f0 = exp2_fast(m_run - mn), f1 = exp2_fast(m2 - mn), fs = merge_slot ? exp2_fast(ms - mn) : 0.f;
-  float *ap = p.st.a + idx * kHeadDim + 64 * th + 4 * lh;
+  GlobalFloat *ap = cx.a + idx * kHeadDim + 64 * th + 4 * lh;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     const int r = 4 * (q & 3), db = q >> 2;
@@ -867,13 +886,13 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
 #pragma unroll
     for (int e = 0; e < 4; ++e) own[e] = th ? acc[2 + db][r + e] : acc[db][r + e];
     f32x4_t o = f0 * own + f1 * sh[((w ^ 1) * 8 + q) * 64 + lane];
-    f32x4_t *dst = reinterpret_cast<f32x4_t *>(ap + 32 * db + 2 * r);
+    GlobalFloat4 *dst = (GlobalFloat4 *)(ap + 32 * db + 2 * r);
     if (merge_slot) o += fs * *dst;
     *dst = o;
   }
   if (th == 0 && lh == 0) {
-    p.st.m[idx] = mn;
-    p.st.l[idx] = f0 * l_run + f1 * l2 + fs * lsl;
+    cx.m[idx] = mn;
+    cx.l[idx] = f0 * l_run + f1 * l2 + fs * lsl;
   }
 }
 
@@ -886,23 +905,20 @@ __device__ __forceinline__ void rows_unit(const P &p, unsigned char *smem, const
 // reduced over the 16 lanes of a DPP row.
 // ---------------------------------------------------------------------------
 template <int MAXR, typename P>
-__device__ __forceinline__ void valu_unit(const P &p, float *smem, const UnitRec &ur, int tx, int g) {
+__device__ __forceinline__ void valu_unit(const P &p, const Ctx &cx, float *smem, const UnitArg &ua, int tx, int g) {
   const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
   const int lane = tx & 63;
   const int c = lane & 15;
   const int tg = lane >> 4;
-  const int i0 = unit_i0(ur.word), nit = unit_nit(ur.word);
-  const int q_row0 = ur.q_row0;
-  const int M = ur.n_cand * p.G;
-  const int ntiles = (int)ur.ntiles;
-  const FirstItem fi = load_first_item(p, ur);   // slot and flags of the whole chain
-  const Item &it = fi.it;
+  const int i0 = unit_i0(ua.word);
+  const int M = unit_cand(ua) * cx.G;
+  const int ntiles = (int)ua.ntiles;
 
   float qf[MAXR][8];
 #pragma unroll
   for (int r = 0; r < MAXR; ++r) {
     if (r < M) {
-      const u32x4_t q4 = reinterpret_cast<const u32x4_t *>(p.q + (size_t)global_row(p, q_row0, g, r) * kHeadDim)[c];
+      const u32x4_t q4 = ((const GlobalU32x4 *)(cx.q + (size_t)global_row(cx, ua.q_row0, g, r) * kHeadDim))[c];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         qf[r][2 * e] = bf16_lo(q4[e]);
@@ -921,9 +937,9 @@ __device__ __forceinline__ void valu_unit(const P &p, float *smem, const UnitRec
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[r][e] = 0.f;
   }
-  const uint32_t stride_b = p.tok_stride * 2;
+  const uint32_t stride_b = cx.stride_b;
   const uint32_t voff = tg * stride_b + 16 * c;
-  const float sl2 = p.scale_log2;
+  const float sl2 = cx.sl2;
 
   // coalesced loads (4 token rows per instruction); tokens past the item read 0
   u32x4_t kr[8], vr[8];
@@ -1000,36 +1016,29 @@ __device__ __forceinline__ void valu_unit(const P &p, float *smem, const UnitRec
   // wave w takes the chain's tiles T = w, w + 4, ...
   int T = w;
   if (T < ntiles) {
-    TileCursor cur;
+    Cursor cur(ua);
     NextTile nx;
-    nx.krs = item_rsrc_at(p, it, fi.k, fi.hs, g);
-    nx.vrs = item_rsrc_at(p, it, fi.v, fi.hs, g);
-    nx.tb = T * kTile;
-    if (T >= tiles_of(it)) {
-      seek(p, i0, nit, cur, T);
-      const Item ic = p.items[i0 + cur.k];
-      nx.krs = item_rsrc(p, ic, item_chunk(ic), g, p.k);
-      nx.vrs = item_rsrc(p, ic, item_chunk(ic), g, p.v);
-      nx.tb = (T - cur.base) * kTile;
+    nx.krs = rows_rsrc(cx, ua.k + (size_t)g * ua.hs, ua.tok_count);
+    nx.vrs = rows_rsrc(cx, ua.v + (size_t)g * ua.hs, ua.tok_count);
+    if (T >= cur.end) {
+      const ItemWords ic = cur.seek(p, i0, T);
+      nx.krs = item_rsrc(p, cx, ic, g, p.k);
+      nx.vrs = item_rsrc(p, cx, ic, g, p.v);
     }
+    nx.tb = (T - cur.base) * kTile;
     load_k(nx);
     load_v(nx);
-    int tb = nx.tb;
-    int count = cur.k == 0 ? it.tok_count : p.items[i0 + cur.k].tok_count;
     for (; T + kWaves < ntiles; T += kWaves) {
-      const int kprev = cur.k;
-      seek(p, i0, nit, cur, T + kWaves);
-      if (cur.k != kprev) {
-        const Item in = p.items[i0 + cur.k];
-        nx.krs = item_rsrc(p, in, item_chunk(in), g, p.k);
-        nx.vrs = item_rsrc(p, in, item_chunk(in), g, p.v);
+      const int tb = nx.tb, count = cur.count;
+      if (T + kWaves >= cur.end) {
+        const ItemWords in = cur.seek(p, i0, T + kWaves);
+        nx.krs = item_rsrc(p, cx, in, g, p.k);
+        nx.vrs = item_rsrc(p, cx, in, g, p.v);
       }
       nx.tb = (T + kWaves - cur.base) * kTile;
       tile(tb, count, std::integral_constant<bool, true>{}, nx);
-      tb = nx.tb;
-      count = p.items[i0 + cur.k].tok_count;
     }
-    tile(tb, count, std::integral_constant<bool, false>{}, nx);
+    tile(nx.tb, cur.count, std::integral_constant<bool, false>{}, nx);
   }
 
   // reduce over the token groups, partials -> LDS
@@ -1055,7 +1064,7 @@ __device__ __forceinline__ void valu_unit(const P &p, float *smem, const UnitRec
     }
   }
   __syncthreads();
-  fold_into_slot<MAXR>(p, it, q_row0, g, M, tx, aw, mw, lw);
+  fold_into_slot<MAXR>(cx, ua, g, M, tx, aw, mw, lw);
 }
 
 constexpr int kValuLdsBytes = kWaves * kMaxValuRows * (kAwPitch + 2) * 4;
@@ -1096,15 +1105,20 @@ template <bool Wide, typename P>
 __global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kChunkLdsBytes];
   __shared__ uint32_t claim_sh;
-  const int y = p.heads_fast ? blockIdx.y : blockIdx.x;     // workgroup of its KV head
-  const int g_own = p.heads_fast ? blockIdx.x : blockIdx.y;  // KV head of its own units
-  // The workgroup's first unit record and the range of its further units
-  // are read together at the start and forced into registers here, so
-  // neither the first unit's loads nor its end wait for a second round of
-  // argument reads.
-  UnitRec ur = p.units[y];
+  // Grid (Hkv, workgroups, 1) or (1, workgroups, Hkv): see the launch.
+  const uint32_t y = blockIdx.y;                       // workgroup of its KV head
+  const int g_own = (int)(blockIdx.x + blockIdx.z);    // KV head of its own units
+  // The workgroup's first unit, the range of its further units and what all
+  // bodies need of the arguments are read in one scalar round trip and forced
+  // into registers here, so that neither the first unit's loads nor its end
+  // wait for another.
+  UnitArg ua = unit_at(p, y);
   uint32_t more0 = p.more[y], more1 = p.more[y + 1];
-  asm volatile("" : "+s"(ur.word), "+s"(ur.ntiles), "+s"(ur.q_row0), "+s"(ur.n_cand), "+s"(more0), "+s"(more1));
+  Ctx cx = {p.q, (GlobalFloat *)p.st.a, (GlobalFloat *)p.st.m, (GlobalFloat *)p.st.l, (uint32_t)p.st.R, p.Hq, p.G,
+            p.g_inv, p.scale_log2, p.tok_stride * 2};
+  asm volatile("" : "+s"(ua.k), "+s"(ua.v), "+s"(ua.hs), "+s"(ua.word), "+s"(ua.ntiles), "+s"(ua.tok_count),
+               "+s"(ua.q_row0), "+s"(ua.cand_slot), "+s"(more0), "+s"(more1), "+s"(cx.q), "+s"(cx.a), "+s"(cx.m),
+               "+s"(cx.l), "+s"(cx.R), "+s"(cx.Hq), "+s"(cx.G), "+s"(cx.g_inv), "+s"(cx.sl2), "+s"(cx.stride_b));
   const uint32_t nclaims = (uint32_t)p.num_tail * (uint32_t)p.Hkv;
   const uint32_t last_claim = nclaims + (uint32_t)p.Hkv * (uint32_t)p.num_wgs - 1u;
   uint32_t u = more0;
@@ -1113,10 +1127,10 @@ __global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
     int g = g_own;
     if (first) {
       first = false;
-      if (unit_nit(ur.word) == 0) continue;   // a workgroup without units of its own
+      if (unit_nit(ua.word) == 0) continue;   // a workgroup without units of its own
     } else if (u < more1) {
       __syncthreads();   // the previous unit's fold has read the LDS this unit restages
-      ur = p.units[u++];
+      ua = unit_at(p, u++);
     } else {
       if (nclaims == 0) break;
       __syncthreads();   // ... and every thread has read the previous claim
@@ -1128,9 +1142,11 @@ __global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
       __syncthreads();
       const uint32_t c = __builtin_amdgcn_readfirstlane(claim_sh);
       if (c >= nclaims) break;
-      const uint32_t t = c / (uint32_t)p.Hkv;
-      ur = p.units[p.tail_first + (int)t];
-      g = (int)(c - t * (uint32_t)p.Hkv);
+      uint32_t hkv = (uint32_t)p.Hkv;
+      asm volatile("" : "+s"(hkv));   // keeps the division's set-up out of the launch's start
+      const uint32_t t = c / hkv;
+      ua = unit_at(p, (uint32_t)p.tail_first + t);
+      g = (int)(c - t * hkv);
     }
     // The bodies derive their per-lane addresses from tx.  Passing it
     // through an empty asm each unit keeps the compiler from computing
@@ -1138,29 +1154,29 @@ __global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
     // across it (that spilled 14 registers and cost 6% on one-unit calls).
     int tx = threadIdx.x;
     asm volatile("" : "+v"(tx));
-    const int kind = unit_kind(ur.word);
+    const int kind = unit_kind(ua.word);
     if constexpr (Wide) {
       if (kind >= kUnitMfma3) {
-        rows_unit(p, smem, ur, tx, g);
+        rows_unit(p, cx, smem, ua, tx, g);
         continue;
       }
     }
     const int nxt = u < more1 ? (int)u : -1;   // the next unit of the workgroup's own list
     if (kind == kUnitMfma2)
-      mfma_unit<2>(p, smem, ur, tx, g, nxt);
+      mfma_unit<2>(p, cx, smem, ua, tx, g, nxt);
     else if (kind == kUnitMfma1)
-      mfma_unit<1>(p, smem, ur, tx, g, nxt);
+      mfma_unit<1>(p, cx, smem, ua, tx, g, nxt);
     else {
       // the VALU body's work grows with the rows it is built for: build it
       // for 1, 2 and 4 rows and take the smallest that holds the unit
-      const int rows = ur.n_cand * p.G;
+      const int rows = unit_cand(ua) * cx.G;
       float *lds = reinterpret_cast<float *>(smem);
       if (rows <= 1)
-        valu_unit<1>(p, lds, ur, tx, g);
+        valu_unit<1>(p, cx, lds, ua, tx, g);
       else if (rows <= 2)
-        valu_unit<2>(p, lds, ur, tx, g);
+        valu_unit<2>(p, cx, lds, ua, tx, g);
       else
-        valu_unit<kMaxValuRows>(p, lds, ur, tx, g);
+        valu_unit<kMaxValuRows>(p, cx, lds, ua, tx, g);
     }
   }
 }
@@ -1385,20 +1401,59 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
-// Table capacities of the launches: a Cohort's whole history call usually
-// fits the small class (config 3: 32 workgroups per KV head, 32 units, 128
-// items), large ragged batches the medium one.
-using ChunkSmall = ChunkParamsT<128, 256, 128>;
-using ChunkMedium = ChunkParamsT<512, 1024, 256>;
+// Kernel arguments of a launch: the header, the units and items in their
+// kernel-argument forms (Fat; as UnitRec and Item in the largest class, whose
+// tables would pass 64 KB) and the ranges of the workgroups' further units.
+// The runtime's argument pool holds about a megabyte and a full one makes the
+// next launch wait, so a launch takes the smallest class that holds it: one
+// unit per workgroup (per-chunk calls, small rounds) the first, 16 x 32768
+// tokens (92 units, 188 items) the second, 64 ragged requests or 32 x 131072
+// tokens (170 and 189 units, 407 and 669 items) the third.
+template <int MaxUnits, int MaxItems, int MaxWgs, bool Fat>
+struct ChunkArgs : ChunkHeader {
+  static constexpr int kUnits = MaxUnits, kItems = MaxItems, kWgs = MaxWgs;
+  static constexpr bool kFat = Fat;
+  uint32_t g_inv;
+  uint32_t more[MaxWgs + 1];
+  std::conditional_t<Fat, UnitArg, UnitRec> units[MaxUnits];
+  std::conditional_t<Fat, ChainItem, Item> items[MaxItems];
+};
+using ChunkTiny = ChunkArgs<64, 72, 64, true>;              // 4.8 KB
+using ChunkSmall = ChunkArgs<96, 192, 64, true>;            // 7.3 KB
+using ChunkMedium = ChunkArgs<192, 704, 64, true>;          // 16 KB
+using ChunkMany = ChunkArgs<512, 1024, 256, true>;          // 35 KB
+using ChunkLarge = ChunkArgs<kMaxUnits, kMaxItems, kMaxWgs, false>;   // 54 KB
 
 template <bool Wide, typename D>
 hipError_t launch_chunk_as(const ChunkParams &p, hipStream_t s) {
   static thread_local D d;
   static_cast<ChunkHeader &>(d) = p;
-  std::memcpy(d.units, p.units, sizeof(UnitRec) * p.num_units);
+  d.g_inv = (65536u + (uint32_t)p.G - 1) / (uint32_t)p.G;
+  if constexpr (D::kFat) {
+    for (int u = 0; u < p.num_units; ++u) {
+      const UnitRec &r = p.units[u];
+      UnitArg &a = d.units[u];
+      a.word = r.word;
+      if (unit_nit(r.word) == 0) continue;
+      const Item &it = p.items[unit_i0(r.word)];
+      const size_t first = (size_t)it.tok_begin * p.tok_stride;
+      a.k = p.k[it.chunk] + first;
+      a.v = p.v[it.chunk] + first;
+      a.hs = p.head_stride[it.chunk];
+      a.ntiles = r.ntiles;
+      a.tok_count = it.tok_count;
+      a.q_row0 = r.q_row0;
+      a.cand_slot = pack_cand_slot(it);
+    }
+    for (int i = 0; i < p.num_items; ++i)
+      d.items[i] = {(uint32_t)p.items[i].tok_begin, (uint32_t)p.items[i].tok_count | (uint32_t)p.items[i].chunk << 24};
+  } else {
+    std::memcpy(d.units, p.units, sizeof(UnitRec) * p.num_units);
+    std::memcpy(d.items, p.items, sizeof(Item) * p.num_items);
+  }
   std::memcpy(d.more, p.more, sizeof(uint32_t) * (p.num_wgs + 1));
-  std::memcpy(d.items, p.items, sizeof(Item) * p.num_items);
-  const dim3 grid = p.heads_fast ? dim3(p.Hkv, p.num_wgs) : dim3(p.num_wgs, p.Hkv);
+  // the heads are the fast grid dimension, or the workgroups are
+  const dim3 grid = p.heads_fast ? dim3(p.Hkv, p.num_wgs, 1) : dim3(1, p.num_wgs, p.Hkv);
   hipLaunchKernelGGL((chunk_attn<Wide, D>), grid, dim3(256), 0, s, d);
   return hipGetLastError();
 }
@@ -1408,11 +1463,11 @@ hipError_t launch_chunk_sized(const ChunkParams &p, hipStream_t s) {
   auto fits = [&](int units, int items, int wgs) {
     return p.num_units <= units && p.num_items <= items && p.num_wgs <= wgs;
   };
+  if (fits(ChunkTiny::kUnits, ChunkTiny::kItems, ChunkTiny::kWgs)) return launch_chunk_as<Wide, ChunkTiny>(p, s);
   if (fits(ChunkSmall::kUnits, ChunkSmall::kItems, ChunkSmall::kWgs)) return launch_chunk_as<Wide, ChunkSmall>(p, s);
   if (fits(ChunkMedium::kUnits, ChunkMedium::kItems, ChunkMedium::kWgs)) return launch_chunk_as<Wide, ChunkMedium>(p, s);
-  const dim3 grid = p.heads_fast ? dim3(p.Hkv, p.num_wgs) : dim3(p.num_wgs, p.Hkv);
-  hipLaunchKernelGGL((chunk_attn<Wide, ChunkParams>), grid, dim3(256), 0, s, p);
-  return hipGetLastError();
+  if (fits(ChunkMany::kUnits, ChunkMany::kItems, ChunkMany::kWgs)) return launch_chunk_as<Wide, ChunkMany>(p, s);
+  return launch_chunk_as<Wide, ChunkLarge>(p, s);
 }
 
 }  // namespace
