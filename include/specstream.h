@@ -172,7 +172,9 @@ ss_status ss_round_init(ss_round **out, const ss_round_desc *desc, const void *q
  * slot's "free" event); if signal_after is non-null it is recorded on
  * copy_stream after the copy (the slot's "ready" event).  src must be
  * page-locked host memory (hipHostMalloc / pinned tensors), else
- * SS_ERR_NOT_PINNED; dst must be device memory.  bytes > 0. */
+ * SS_ERR_NOT_PINNED; dst must be device memory.  bytes > 0.  Up to 64 MiB
+ * between 16-byte-aligned addresses the copy is a kernel of 16 workgroups on
+ * copy_stream (the pipeline's uploads too), otherwise the copy engine's. */
 ss_status ss_upload_chunk(void *dst_device, const void *src_pinned_host, size_t bytes,
                           hipStream_t copy_stream, hipEvent_t wait_before, hipEvent_t signal_after);
 

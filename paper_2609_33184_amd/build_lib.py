@@ -31,9 +31,10 @@ def build(verbose: bool = True) -> str:
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
     objs = []
-    kobj = os.path.join(bdir, "ss_kernels.o")
-    _run([HIPCC, *COMMON, *DEVICE_ONLY, "-c", os.path.join(CSRC, "ss_kernels.hip"), "-o", kobj])
-    objs.append(kobj)
+    for name in ("ss_kernels", "ss_copy"):
+        kobj = os.path.join(bdir, name + ".o")
+        _run([HIPCC, *COMMON, *DEVICE_ONLY, "-c", os.path.join(CSRC, name + ".hip"), "-o", kobj])
+        objs.append(kobj)
     for name in ("ss_host", "ss_tier", "ss_width"):
         hobj = os.path.join(bdir, name + ".o")
         _run([HIPCC, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",

@@ -711,7 +711,13 @@ ss_status enqueue_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind k
   if (wait_before != nullptr && (e = hipStreamWaitEvent(copy_stream, wait_before, 0)) != hipSuccess)
     return hip_fail(e, "hipStreamWaitEvent (copy)");
   if (enqueued != nullptr) *enqueued = wait_before != nullptr;
-  if ((e = hipMemcpyAsync(dst, src, bytes, kind, copy_stream)) != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+  const void *mapped =
+      kind == hipMemcpyHostToDevice && ss::upload_source != nullptr ? ss::upload_source(dst, src, bytes, copy_stream) : nullptr;
+  if (mapped != nullptr) {
+    if ((e = ss::launch_upload(dst, mapped, bytes, copy_stream)) != hipSuccess) return hip_fail(e, "upload kernel launch");
+  } else if ((e = hipMemcpyAsync(dst, src, bytes, kind, copy_stream)) != hipSuccess) {
+    return hip_fail(e, "hipMemcpyAsync");
+  }
   if (enqueued != nullptr) *enqueued = true;
   if (signal_after != nullptr && (e = hipEventRecord(signal_after, copy_stream)) != hipSuccess)
     return hip_fail(e, "hipEventRecord (copy)");

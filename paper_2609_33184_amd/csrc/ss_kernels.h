@@ -156,6 +156,14 @@ hipError_t launch_finalize(const FinalParams &p, hipStream_t s);
 // captured in a graph).
 hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t s);
 
+// Upload by kernel.  upload_source: the address at which the GPU that `s`
+// belongs to sees the pinned range [src, src + bytes), if the range and dst's
+// are mapped for it whole and 16-byte aligned; null if the copy engine has to
+// do the upload.  launch_upload copies from such an address.  Weak: without
+// the kernels linked in, every upload goes to the copy engine.
+const void *upload_source(const void *dst, const void *src, uint64_t bytes, hipStream_t s) __attribute__((weak));
+hipError_t launch_upload(void *dst, const void *mapped_src, uint64_t bytes, hipStream_t s) __attribute__((weak));
+
 // Read-bandwidth probe over `bytes` (a multiple of 16) of device memory:
 // workgroup w < workgroups XOR-folds bytes [w * share, (w + 1) * share)
 // (share a multiple of 16, at most kProbeMaxShare) into sink[w].
