@@ -146,7 +146,8 @@ typedef struct {
 #define SS_KV_HEAD_MAJOR_KV 2
 
 /* Bytes of device workspace a round with this descriptor needs (fp32
- * online-softmax states of every query row, per split slot, then a 256-byte
+ * online-softmax states of every query row, per split slot (32 of them; 64 or
+ * 128 in rounds of at most 4 (request, KV head) pairs), then a 256-byte
  * counter block whose first word is the balancing tail's claim counter).  0
  * if the descriptor is invalid (see ss_last_error). */
 size_t ss_round_workspace_bytes(const ss_round_desc *desc);

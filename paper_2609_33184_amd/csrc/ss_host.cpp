@@ -67,6 +67,10 @@ constexpr long kTargetWorkgroups = 256;
 // against 17.0 us with 64 slots, which made finalize slower.
 constexpr long kSmallShare = 2048;
 constexpr int kMinPiece = 128;
+// A request split into more than the base slots (see num_slots) keeps shares
+// of this many tokens: 1 x 32768 tokens with 2 KV heads took 21.1 us with 32 or
+// 64 shares of 1024 or 512 tokens and 22.4 us with 128 of 256.
+constexpr long kMinManyShare = 512;
 // Balancing tail (see the history kernel): the last kDefaultTailPermille
 // thousandths of every share become tail units of guided sizes, each about
 // 2 (tail tokens left) / W tokens, clamped to [kTailMin, kTailMax] and to
@@ -133,20 +137,39 @@ ss_status validate_desc(const ss_round_desc *d) {
                   SS_MAX_ROWS_PER_KV_HEAD);
     rows += (long)n * d->num_q_heads;
   }
-  if (rows * (long)ss::kNumSlots * ss::kHeadDim > (1L << 40))
+  if (rows * (long)ss::kBaseSlots * ss::kHeadDim > (1L << 40))
     return fail(SS_ERR_INVALID_ARGUMENT, "round too large");
   if (rows * ss::kHeadDim * 2 >= (1L << 31))   // the kernels address Q with 32-bit byte offsets
     return fail(SS_ERR_INVALID_ARGUMENT, "round too large: the query tensor must stay below 2^31 bytes");
   return SS_OK;
 }
 
+// State slots per query row.  A request's workgroups for one KV head each own a
+// slot, so 32 slots give a round of few requests and KV heads 32 B Hkv
+// workgroups at most.  At B Hkv <= 4 that leaves half of the 256 CUs without
+// one, and the round gets 64 or 128 slots (at most 256 rows then: 17 MB).
+// Rounds back to back, 32 slots against 64 or 128 as plan_chunks uses them:
+// 1 x 131072 tokens, 32q/4kv 77.8 -> 54.1 us, 8q/2kv 55.7 -> 31.0 us; 1 x 32768,
+// 32q/4kv, 6 candidates 27.2 -> 21.3 us, 4 candidates 21.4 -> 19.7 us.  More
+// slots where the CUs are full only lengthen finalize: 1 x 32768, 32q/8kv 28.6
+// us with 32, 30.4 us with 64.
+long num_slots(long B, long Hkv) {
+  const long pairs = B * Hkv;
+  return pairs > 4 ? ss::kBaseSlots : pairs > 2 ? 2 * ss::kBaseSlots : ss::kNumSlots;
+}
+
 // Workspace: slot states a, m, l, then the counter block of kClaimCounters
 // words (the first is the balancing tail's claim counter).
-size_t workspace_bytes_rows(long R) {
-  const size_t a = align_up((size_t)ss::kNumSlots * R * ss::kHeadDim * sizeof(float), 256);
-  const size_t m = align_up((size_t)ss::kNumSlots * R * sizeof(float), 256);
-  return a + 2 * m + align_up(ss::kClaimCounters * sizeof(uint32_t), 256);
-}
+struct WorkspaceLayout {
+  size_t m, l, counters, bytes;   // offsets (a is at 0) and the whole size
+  WorkspaceLayout(long R, long B, long Hkv) {
+    const size_t rows = (size_t)num_slots(B, Hkv) * R;
+    m = align_up(rows * ss::kHeadDim * sizeof(float), 256);
+    l = m + align_up(rows * sizeof(float), 256);
+    counters = l + align_up(rows * sizeof(float), 256);
+    bytes = counters + align_up(ss::kClaimCounters * sizeof(uint32_t), 256);
+  }
+};
 
 }  // namespace
 
@@ -214,7 +237,7 @@ ss_status check_history_args(const ss_round *r, int nchunks, const void *const *
   if (nchunks < 1 || nchunks > ss::kMaxChunks)
     return fail(SS_ERR_INVALID_ARGUMENT, "num_chunks = %d outside [1, %d]", nchunks, ss::kMaxChunks);
   if (len == nullptr) return fail(SS_ERR_INVALID_ARGUMENT, "len is null");
-  const long cap = max_piece_tokens(r) * ss::kNumSlots;
+  const long cap = max_piece_tokens(r) * ss::kBaseSlots;
   tot->assign(nchunks, 0);
   for (int c = 0; c < nchunks; ++c) {
     long t = 0;
@@ -275,9 +298,9 @@ int kind_of(const ss_round *r, int b) {
 // (a remainder below tail_min joins the piece before it).
 // Each request's part of a share or piece becomes units: its token ranges,
 // cut at chunk boundaries and at pmax tokens, in chains of at most
-// kMaxChain.  Returns false if a request would need more than kNumSlots
+// kMaxChain.  Returns false if a request would need more than max_slots
 // slots.
-bool build_plan(const ss_round *r, int nchunks, const int32_t *len, long W, long pmax, int tail_permille,
+bool build_plan(const ss_round *r, int nchunks, const int32_t *len, long W, long pmax, int max_slots, int tail_permille,
                 long tail_min, Plan *plan) {
   const int B = r->B;
   *plan = Plan();
@@ -338,7 +361,7 @@ bool build_plan(const ss_round *r, int nchunks, const int32_t *len, long W, long
         for (long q = 0; q < take;) {
           if (ranges == ss::kMaxChain) close();
           if (ranges == 0) {
-            if (slot[b] >= ss::kNumSlots) return false;
+            if (slot[b] >= max_slots) return false;
             ub = b;
           }
           const long n = std::min(take - q, pmax);
@@ -414,12 +437,22 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, const 
   }
   W = std::max<long>(1, std::min<long>(W, total));
   const long pmax = max_piece_tokens(r);
+  // Past the base slots only while the shares keep kMinManyShare tokens.
+  int max_slots = ss::kBaseSlots;
+  if (r->split_tokens == 0) {
+    const long slots = num_slots(r->B, r->Hkv);
+    const long many = std::min({kTargetWorkgroups / r->Hkv, total / kMinManyShare, slots * r->B});
+    if (slots > ss::kBaseSlots && many > ss::kBaseSlots) {
+      max_slots = (int)slots;
+      W = many;
+    }
+  }
   // Fewer, larger shares until every request fits its units into the
   // slots; more, smaller ones while a share would exceed one launch's unit
   // or item table.
   bool shrunk = false;
   for (;;) {
-    if (!build_plan(r, nchunks, len, W, pmax, 0, kTailMin, plan)) {
+    if (!build_plan(r, nchunks, len, W, pmax, W == 1 ? ss::kBaseSlots : max_slots, 0, kTailMin, plan)) {
       if (W == 1) return fail(SS_ERR_INVALID_ARGUMENT, "too many token ranges per request for one history call");
       W = (W + 1) / 2;
       shrunk = true;
@@ -442,7 +475,7 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, const 
   if (permille > 0 && total / W >= min_share && fits_one_launch(*plan)) {
     Plan t;
     for (long tmin = kTailMin; tmin <= kTailMax; tmin *= 2)
-      if (build_plan(r, nchunks, len, W, pmax, permille, tmin, &t) && fits_one_launch(t)) {
+      if (build_plan(r, nchunks, len, W, pmax, ss::kBaseSlots, permille, tmin, &t) && fits_one_launch(t)) {
         *plan = std::move(t);
         break;
       }
@@ -747,7 +780,7 @@ size_t ss_round_workspace_bytes(const ss_round_desc *desc) {
   if (validate_desc(desc) != SS_OK) return 0;
   long R = 0;
   for (int b = 0; b < desc->num_requests; ++b) R += (long)desc->num_cand[b] * desc->num_q_heads;
-  return workspace_bytes_rows(R);
+  return WorkspaceLayout(R, desc->num_requests, desc->num_kv_heads).bytes;
 }
 
 }  // extern "C"
@@ -766,7 +799,8 @@ ss_status init_round(ss_round **out, const ss_round_desc *desc, const void *q, v
   if (q == nullptr || !aligned(q, 16)) return fail(SS_ERR_INVALID_ARGUMENT, "q must be non-null and 16-byte aligned");
   long R = 0;
   for (int b = 0; b < desc->num_requests; ++b) R += (long)desc->num_cand[b] * desc->num_q_heads;
-  const size_t need = workspace_bytes_rows(R);
+  const WorkspaceLayout layout(R, desc->num_requests, desc->num_kv_heads);
+  const size_t need = layout.bytes;
   if (workspace == nullptr || !aligned(workspace, 256))
     return fail(SS_ERR_WORKSPACE, "workspace must be non-null and 256-byte aligned");
   if (workspace_bytes < need)
@@ -797,12 +831,10 @@ ss_status init_round(ss_round **out, const ss_round_desc *desc, const void *q, v
   }
   r->q = static_cast<const uint16_t *>(q);
   char *ws = static_cast<char *>(workspace);
-  const size_t a_bytes = align_up((size_t)ss::kNumSlots * R * ss::kHeadDim * sizeof(float), 256);
-  const size_t m_bytes = align_up((size_t)ss::kNumSlots * R * sizeof(float), 256);
   r->st.a = reinterpret_cast<float *>(ws);
-  r->st.m = reinterpret_cast<float *>(ws + a_bytes);
-  r->st.l = reinterpret_cast<float *>(ws + a_bytes + m_bytes);
-  r->counters = reinterpret_cast<uint32_t *>(ws + a_bytes + 2 * m_bytes);
+  r->st.m = reinterpret_cast<float *>(ws + layout.m);
+  r->st.l = reinterpret_cast<float *>(ws + layout.l);
+  r->counters = reinterpret_cast<uint32_t *>(ws + layout.counters);
   r->counters_ready = desc->counters_zeroed != 0;
   r->tail_permille = desc->balance_permille;
   r->st.R = (int32_t)R;

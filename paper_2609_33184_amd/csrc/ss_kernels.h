@@ -7,7 +7,8 @@
 namespace ss {
 
 constexpr int kHeadDim = 128;       // d
-constexpr int kNumSlots = 32;       // split slots of the running state per row
+constexpr int kNumSlots = 128;      // most split slots of the running state per row (see num_slots)
+constexpr int kBaseSlots = 32;      // slots of a round with many rows
 constexpr int kMaxItems = 2048;     // work items per launch (kernel-argument list)
 constexpr int kMaxUnits = 1024;     // units per launch (x all KV heads)
 constexpr int kMaxWgs = 1024;       // workgroups per KV head per launch

@@ -14,7 +14,7 @@
 //     (two bf16 MFMAs), which keeps P to ~2^-16 relative; rounding P once to
 //     bf16 would cost ~1.6e-3 relative L2 error.  The denominator l sums the
 //     fp32 weights themselves, which hi + lo carry to that precision.
-//   * a running state is split into kNumSlots slots per query row so that
+//   * a running state is split into 32 to 128 slots per query row so that
 //     several workgroups can fold disjoint token ranges of one chunk into the
 //     same row without atomics; the finalize kernel merges the slots.
 #include <hip/hip_runtime.h>
@@ -1070,7 +1070,6 @@ __device__ __forceinline__ void valu_unit(const P &p, const Ctx &cx, float *smem
 constexpr int kValuLdsBytes = kWaves * kMaxValuRows * (kAwPitch + 2) * 4;
 constexpr int kChunkLdsBytes = MfmaLds<2>::kBytes > kValuLdsBytes ? MfmaLds<2>::kBytes : kValuLdsBytes;
 static_assert(MfmaLds<1>::kBytes <= kChunkLdsBytes, "LDS sizes");
-static_assert(kNumSlots == 32, "finalize builds for 8, 16, 24 and 32 slots");
 static_assert(kRowsLdsBytes <= kChunkLdsBytes && 2 * kChunkLdsBytes <= 160 * 1024, "LDS sizes");
 
 // ---------------------------------------------------------------------------
@@ -1235,7 +1234,7 @@ __global__ void __launch_bounds__(256) finalize_kernel(const P p) {
   asm volatile("" : "+s"(pair), "+s"(cand0), "+s"(g_magic), "+s"(g_mask), "+s"(R), "+s"(Hq), "+s"(kstep), "+s"(q_ptr),
                "+s"(k_ptr), "+s"(v_ptr), "+s"(m_ptr), "+s"(l_ptr), "+s"(a_ptr), "+s"(out), "+s"(lse), "+s"(scale_log2));
   const uint32_t word = pair >> (16 * (c & 1));
-  const uint32_t i = word & 7u, nslot = (word >> 3) & 0x3fu;
+  const uint32_t i = word & 7u, nslot = (word >> 3) & 0xffu;
   const uint32_t cg = cand0 + c;                                   // packed candidate row
   const uint32_t h = Split == 1 ? 2 * (blockIdx.x * kWaves + w) + half : 2 * blockIdx.x + half;
   const uint32_t hc = h < Hq ? h : Hq - 1;                         // lanes past the heads redo the last one
@@ -1419,8 +1418,8 @@ struct ChunkArgs : ChunkHeader {
   std::conditional_t<Fat, ChainItem, Item> items[MaxItems];
 };
 using ChunkTiny = ChunkArgs<64, 72, 64, true>;              // 4.8 KB
-using ChunkSmall = ChunkArgs<96, 192, 64, true>;            // 7.3 KB
-using ChunkMedium = ChunkArgs<192, 704, 64, true>;          // 16 KB
+using ChunkSmall = ChunkArgs<128, 192, 128, true>;          // 9 KB
+using ChunkMedium = ChunkArgs<256, 704, 256, true>;         // 20 KB
 using ChunkMany = ChunkArgs<512, 1024, 256, true>;          // 35 KB
 using ChunkLarge = ChunkArgs<kMaxUnits, kMaxItems, kMaxWgs, false>;   // 54 KB
 
@@ -1486,7 +1485,7 @@ hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t s) {
 namespace {
 
 // What finalize_kernel reads: candidate c's word holds its index within its
-// request (3 bits) and the request's slot count (6 bits), two per dword.
+// request (3 bits) and the request's slot count (8 bits), two per dword.
 template <int MaxCand>
 struct FinalArgs : FinalHeader {
   static constexpr int kCand = MaxCand;
@@ -1497,7 +1496,7 @@ struct FinalArgs : FinalHeader {
 };
 using FinalSmall = FinalArgs<128>;
 using FinalLarge = FinalArgs<4096>;
-static_assert(kMaxCand <= 8 && kNumSlots <= 32, "candidate word fields, a lane per slot");
+static_assert(kMaxCand <= 8 && kNumSlots < 256 && kNumSlots <= 4 * 32 && kBaseSlots == 32, "candidate word fields, a lane per slot of a wave");
 
 template <int MS, int Split, bool Huge, typename D>
 hipError_t launch_finalize_as(const D &d, int n, hipStream_t s) {
@@ -1513,7 +1512,7 @@ template <int Split, typename D>
 hipError_t launch_finalize_split(const D &d, int n, int slots, hipStream_t s) {
   if (slots <= 8) return launch_finalize_as<8, Split, false>(d, n, s);
   if (slots <= 16) return launch_finalize_as<16, Split, false>(d, n, s);
-  return launch_finalize_as<kNumSlots, Split, false>(d, n, s);
+  return launch_finalize_as<kBaseSlots, Split, false>(d, n, s);
 }
 
 // Rows are split over a workgroup's waves while that takes at most this many
@@ -1528,8 +1527,11 @@ constexpr long kSplitWgs = 1024;
 
 template <typename D>
 hipError_t launch_finalize_cand(const D &d, int n, int slots, hipStream_t s) {
-  if ((uint64_t)kNumSlots * (uint32_t)d.st.R * (kHeadDim * 4) >= (uint64_t(1) << 32))
-    return launch_finalize_as<kNumSlots, 1, true>(d, n, s);
+  // more slots than a half wave has lanes (rounds of few rows) are always split
+  if (slots > 64) return launch_finalize_as<kNumSlots, 4, false>(d, n, s);
+  if (slots > kBaseSlots) return launch_finalize_as<64, 4, false>(d, n, s);
+  if ((uint64_t)kBaseSlots * (uint32_t)d.st.R * (kHeadDim * 4) >= (uint64_t(1) << 32))
+    return launch_finalize_as<kBaseSlots, 1, true>(d, n, s);
   if constexpr (D::kCand <= FinalSmall::kCand)
     if ((long)n * ((d.Hq + 1) / 2) <= kSplitWgs) return launch_finalize_split<4>(d, n, slots, s);
   return launch_finalize_split<1>(d, n, slots, s);

@@ -1,0 +1,34 @@
+// The planner's checks (plan_check.cpp) on rounds of at most 4 (request, KV
+// head) pairs, which have 64 or 128 state slots: every history call of the
+// scenarios covers every token once, writes dense slots below the round's
+// count and stays inside its chunks, through both ways of starting a round.
+#define main plan_check_main
+#include "plan_check.cpp"
+#undef main
+
+int main() {
+  std::mt19937 rng(5);
+  for (int layout : {SS_KV_TOKEN_MAJOR, SS_KV_HEAD_MAJOR_KV}) {
+    // 256 / Hkv workgroups per KV head while a share keeps 512 tokens
+    scenario("1 x 131072, 2 KV heads (128 slots)", 1, 8, 2, {8}, {131072}, 8192, 0, layout, 16, 0, 0, 0, 128);
+    scenario("1 x 32768, 4 KV heads (64 slots)", 1, 32, 4, {6}, {32768}, 4096, 0, layout, 8, 0, 0, 0, 64);
+    scenario("1 x 20000, 4 KV heads (39 shares)", 1, 32, 4, {4}, {20000}, 4096, 0, layout, 8, 0, 0, 0, 39);
+    scenario("1 x 16384, 4 KV heads (32 slots)", 1, 32, 4, {4}, {16384}, 4096, 0, layout, 8, 0, 0, 0, 32);
+    scenario("4 x 70000, 1 KV head", 4, 8, 1, {8, 1, 3, 5}, {70000, 1, 40000, 33}, 9000, 0, layout, 8);
+    scenario("1 x 400000, 1 KV head", 1, 8, 1, {8}, {400000}, 20000, 0, layout, 20);
+    scenario("per-chunk calls", 1, 32, 4, {8}, {100000}, 40000, 0, layout, 1);
+    scenario("caller's shares keep 32 slots", 1, 8, 2, {5}, {65536}, 4096, 512, layout, 16, 0, 0, -1, 32);
+    for (int rep = 0; rep < 60; ++rep) {
+      const int hkv = 1 + rng() % 4, B = 1 + rng() % (4 / hkv), G = 1 + rng() % 8;
+      std::vector<int> nc(B), h(B);
+      for (int b = 0; b < B; ++b) { nc[b] = 1 + rng() % 8; h[b] = (int)(rng() % (rep % 3 ? 90000 : 700)); }
+      const int S = 32 * (1 + rng() % 512);
+      int nch = 0;
+      for (int x : h) nch = std::max(nch, (x + S - 1) / S);
+      if (nch == 0 || nch > 2000) continue;
+      scenario("random", B, G * hkv, hkv, nc, h, S, rng() % 4 ? 0 : 32 * (1 + rng() % 64), layout, 1 + rng() % 32);
+    }
+  }
+  printf("%s\n", fails ? "FAILURES" : "all ok");
+  return fails ? 1 : 0;
+}
