@@ -1423,8 +1423,27 @@ using ChunkMedium = ChunkArgs<256, 704, 256, true>;         // 20 KB
 using ChunkMany = ChunkArgs<512, 1024, 256, true>;          // 35 KB
 using ChunkLarge = ChunkArgs<kMaxUnits, kMaxItems, kMaxWgs, false>;   // 54 KB
 
+// Workgroups per KV head.  A share that spans requests is several units, and
+// where a share is a few tiles, its workgroup spends more time starting the
+// second unit than attending it (the units of 24 requests of 33 to 3000 tokens
+// ended within 13 us of the launch's start, those that came second at 22).
+// Such a launch, of at most kSpreadTiles tiles per share, gives every unit a
+// workgroup, if they nearly all run at once (two per CU).  Rounds back to back,
+// without and with: those 24 requests in one call (7 tiles a share, 688
+// workgroups) 25.6 -> 23.7 us, by chunk 47.4 -> 36.5 us.  Longer shares are
+// balanced as they are, and their units are not: 12 requests of 100 to 20000
+// tokens 24.1 us as shares, 26.5 us as units, 16 of 1000 to 16000 53.3 and 62.7.
+constexpr long kSpreadTiles = 8;
+constexpr long kSpreadWgs = 768;
+int launch_wgs(const ChunkParams &p) {
+  if (p.num_tail > 0 || (long)p.num_units * p.Hkv > kSpreadWgs) return p.num_wgs;
+  long tiles = 0;
+  for (int u = 0; u < p.num_units; ++u) tiles += p.units[u].ntiles;
+  return tiles <= kSpreadTiles * p.num_wgs ? p.num_units : p.num_wgs;
+}
+
 template <bool Wide, typename D>
-hipError_t launch_chunk_as(const ChunkParams &p, hipStream_t s) {
+hipError_t launch_chunk_as(const ChunkParams &p, int wgs, hipStream_t s) {
   static thread_local D d;
   static_cast<ChunkHeader &>(d) = p;
   d.g_inv = (65536u + (uint32_t)p.G - 1) / (uint32_t)p.G;
@@ -1450,23 +1469,28 @@ hipError_t launch_chunk_as(const ChunkParams &p, hipStream_t s) {
     std::memcpy(d.units, p.units, sizeof(UnitRec) * p.num_units);
     std::memcpy(d.items, p.items, sizeof(Item) * p.num_items);
   }
-  std::memcpy(d.more, p.more, sizeof(uint32_t) * (p.num_wgs + 1));
+  if (wgs == p.num_wgs) {
+    std::memcpy(d.more, p.more, sizeof(uint32_t) * (wgs + 1));
+  } else {                            // a workgroup per unit: none has a further one
+    for (int w = 0; w <= wgs; ++w) d.more[w] = (uint32_t)p.num_units;
+  }
   // the heads are the fast grid dimension, or the workgroups are
-  const dim3 grid = p.heads_fast ? dim3(p.Hkv, p.num_wgs, 1) : dim3(1, p.num_wgs, p.Hkv);
+  const dim3 grid = p.heads_fast ? dim3(p.Hkv, wgs, 1) : dim3(1, wgs, p.Hkv);
   hipLaunchKernelGGL((chunk_attn<Wide, D>), grid, dim3(256), 0, s, d);
   return hipGetLastError();
 }
 
 template <bool Wide>
 hipError_t launch_chunk_sized(const ChunkParams &p, hipStream_t s) {
-  auto fits = [&](int units, int items, int wgs) {
-    return p.num_units <= units && p.num_items <= items && p.num_wgs <= wgs;
+  const int wgs = launch_wgs(p);
+  auto fits = [&](int units, int items, int max_wgs) {
+    return p.num_units <= units && p.num_items <= items && wgs <= max_wgs;
   };
-  if (fits(ChunkTiny::kUnits, ChunkTiny::kItems, ChunkTiny::kWgs)) return launch_chunk_as<Wide, ChunkTiny>(p, s);
-  if (fits(ChunkSmall::kUnits, ChunkSmall::kItems, ChunkSmall::kWgs)) return launch_chunk_as<Wide, ChunkSmall>(p, s);
-  if (fits(ChunkMedium::kUnits, ChunkMedium::kItems, ChunkMedium::kWgs)) return launch_chunk_as<Wide, ChunkMedium>(p, s);
-  if (fits(ChunkMany::kUnits, ChunkMany::kItems, ChunkMany::kWgs)) return launch_chunk_as<Wide, ChunkMany>(p, s);
-  return launch_chunk_as<Wide, ChunkLarge>(p, s);
+  if (fits(ChunkTiny::kUnits, ChunkTiny::kItems, ChunkTiny::kWgs)) return launch_chunk_as<Wide, ChunkTiny>(p, wgs, s);
+  if (fits(ChunkSmall::kUnits, ChunkSmall::kItems, ChunkSmall::kWgs)) return launch_chunk_as<Wide, ChunkSmall>(p, wgs, s);
+  if (fits(ChunkMedium::kUnits, ChunkMedium::kItems, ChunkMedium::kWgs)) return launch_chunk_as<Wide, ChunkMedium>(p, wgs, s);
+  if (fits(ChunkMany::kUnits, ChunkMany::kItems, ChunkMany::kWgs)) return launch_chunk_as<Wide, ChunkMany>(p, wgs, s);
+  return launch_chunk_as<Wide, ChunkLarge>(p, wgs, s);
 }
 
 }  // namespace
