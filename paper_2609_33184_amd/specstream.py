@@ -11,7 +11,9 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional, Sequence
+from array import array
+from itertools import chain
+from typing import Iterable, Optional, Sequence
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libspecstream.so")
 _lib: Optional[ctypes.CDLL] = None
@@ -99,16 +101,16 @@ def load() -> ctypes.CDLL:
         "ss_round_workspace_bytes": (SZ, [ctypes.POINTER(ss_round_desc)]),
         "ss_round_init": (I32, [ctypes.POINTER(P), ctypes.POINTER(ss_round_desc), P, P, SZ, P]),
         "ss_upload_chunk": (I32, [P, P, SZ, P, P, P]),
-        "ss_attend_history_chunk": (I32, [P, P, P, PI32, P, P, P]),
-        "ss_attend_history_chunks": (I32, [P, I32, ctypes.POINTER(P), ctypes.POINTER(P), PI32, P, P, P]),
+        "ss_attend_history_chunk": (I32, [P, P, P, P, P, P, P]),
+        "ss_attend_history_chunks": (I32, [P, I32, ctypes.POINTER(P), ctypes.POINTER(P), P, P, P, P]),
         "ss_attend_local_candidates": (I32, [P, P, P, P]),
         "ss_round_finalize": (I32, [P, P, P, P]),
         "ss_round_init_scratch": (I32, [ctypes.POINTER(P), ctypes.POINTER(ss_round_desc), P, P]),
         "ss_probe_read": (I32, [P, SZ, P, I32, P]),
         "ss_round_destroy": (None, [P]),
         "ss_pipeline_create": (I32, [ctypes.POINTER(P), P, P, SZ, P]),
-        "ss_pipeline_attend_chunk": (I32, [P, P, P, PI32, P]),
-        "ss_pipeline_attend_chunks": (I32, [P, P, I32, P, PI32, P]),
+        "ss_pipeline_attend_chunk": (I32, [P, P, P, P, P]),
+        "ss_pipeline_attend_chunks": (I32, [P, P, I32, P, P, P]),
         "ss_pipeline_destroy": (None, [P]),
         "ss_event_create": (I32, [ctypes.POINTER(P)]),
         "ss_event_destroy": (None, [P]),
@@ -146,6 +148,16 @@ def _lens(len_: Sequence[int]):
     return (ctypes.c_int32 * len(len_))(*[int(x) for x in len_])
 
 
+def _counts(values: Iterable[int], fallback) -> array:
+    """Token counts as a C int array, filled without a Python object per count;
+    values that only int() takes (and counts beyond 32 bits, which the library
+    refuses) go through ``fallback()``, their list."""
+    try:
+        return array("i", iter(values))
+    except (TypeError, OverflowError):
+        return array("i", bytes((ctypes.c_int32 * len(fb))(*[int(x) for x in fb])) if (fb := fallback()) else b"")
+
+
 # ---------------------------------------------------------------------------
 # entry points (same names as the C ABI)
 # ---------------------------------------------------------------------------
@@ -176,7 +188,8 @@ def ss_upload_chunk(dst_device: int, src_pinned_host: int, nbytes: int, copy_str
 
 def ss_attend_history_chunk(r: int, k: int, v: int, len_: Sequence[int], wait_before: Optional[int] = None,
                             signal_after: Optional[int] = None, stream: int = 0) -> None:
-    _check(load().ss_attend_history_chunk(r, k, v, _lens(len_), wait_before, signal_after, stream),
+    a = _counts(len_, lambda: list(len_))
+    _check(load().ss_attend_history_chunk(r, k, v, a.buffer_info()[0], wait_before, signal_after, stream),
            "ss_attend_history_chunk")
 
 
@@ -186,9 +199,9 @@ def ss_attend_history_chunks(r: int, k: Sequence[int], v: Sequence[int], lens: S
     n = len(k)
     kp = (ctypes.c_void_p * n)(*k)
     vp = (ctypes.c_void_p * n)(*v)
-    flat = [int(x) for row in lens for x in row]
-    _check(load().ss_attend_history_chunks(r, n, kp, vp, (ctypes.c_int32 * len(flat))(*flat), wait_before,
-                                           signal_after, stream), "ss_attend_history_chunks")
+    a = _counts(chain.from_iterable(lens), lambda: [x for row in lens for x in row])
+    _check(load().ss_attend_history_chunks(r, n, kp, vp, a.buffer_info()[0], wait_before, signal_after, stream),
+           "ss_attend_history_chunks")
 
 
 def ss_attend_local_candidates(r: int, k_cand: int, v_cand: int, stream: int = 0) -> None:
@@ -221,12 +234,13 @@ def ss_pipeline_create(staging0: int, staging1: int, slot_bytes: int, copy_strea
 
 
 def ss_pipeline_attend_chunk(p: int, r: int, host_kv: int, len_: Sequence[int], stream: int = 0) -> None:
-    _check(load().ss_pipeline_attend_chunk(p, r, host_kv, _lens(len_), stream), "ss_pipeline_attend_chunk")
+    a = _counts(len_, lambda: list(len_))
+    _check(load().ss_pipeline_attend_chunk(p, r, host_kv, a.buffer_info()[0], stream), "ss_pipeline_attend_chunk")
 
 
 def ss_pipeline_attend_chunks(p: int, r: int, host_kv: int, lens: Sequence[Sequence[int]], stream: int = 0) -> None:
-    flat = [int(x) for row in lens for x in row]
-    _check(load().ss_pipeline_attend_chunks(p, r, len(lens), host_kv, (ctypes.c_int32 * len(flat))(*flat), stream),
+    a = _counts(chain.from_iterable(lens), lambda: [x for row in lens for x in row])
+    _check(load().ss_pipeline_attend_chunks(p, r, len(lens), host_kv, a.buffer_info()[0], stream),
            "ss_pipeline_attend_chunks")
 
 
