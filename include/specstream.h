@@ -92,10 +92,11 @@ typedef struct {
                                tokens (all requests, in request order) are
                                split into equal shares of about this many,
                                one per workgroup and KV head; 0 = automatic
-                               (one workgroup per CU, two per CU for calls
-                               whose shares would be below 2048 tokens or
-                               with a request of more than 32 rows per KV
-                               head);
+                               (one workgroup per CU; two per CU for calls
+                               with a request of more than 32 rows per KV head
+                               and for calls of short shares, below 2048
+                               tokens, that span requests or have 1 or 2 rows
+                               per KV head);
                                else a multiple of 32                           */
   int32_t mfma_min_rows;    /* rows per KV head (n_b * G) from which the bf16
                                MFMA path is used; fewer (at most 4) use the

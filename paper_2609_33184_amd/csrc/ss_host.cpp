@@ -57,15 +57,21 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // per-request pieces in longest-first order and 678-681 us with equal
 // shares (same GPU, same run).
 constexpr long kTargetWorkgroups = 256;
-// Calls whose shares would be shorter than kSmallShare tokens at one
-// workgroup per CU are latency-bound: each wave walks its few tiles one
-// HBM round trip after another.  They get twice the workgroups (two fit on
-// a CU), with shares of at least kMinPiece tokens (one tile per wave), as
-// far as the state slots allow.  Measured on MI355X: 1 x 4096 tokens, 2 KV
-// heads, one batched call, 9.9 -> 7.5 us (64 workgroups instead of 32);
-// 1 x 16384 tokens, 8 KV heads (which would need 64 slots) took 16.5
-// against 17.0 us with 64 slots, which made finalize slower.
+// Calls whose shares would be shorter than kSmallShare tokens at one workgroup
+// per CU get twice the workgroups (two fit on a CU) if many shares span
+// requests: while one of a CU's workgroups goes from unit to unit, the other
+// streams.  That is more than every second share, or in shares below kTinyShare
+// tokens every fourth.  So do calls with units of the VALU body, which keeps
+// fewer loads in flight.  A share that is one unit gains nothing from a second
+// workgroup beside it and pays twice for query staging, merge and fold.  Rounds
+// back to back, one against two per CU: 24 requests of 33 to 3000 tokens 27.7
+// and 23.2 us, 64 of 100 to 1500 39.8 and 36.4, 8 of 200 to 8000 19.9 and 19.2,
+// 8 x 8191 with one row per KV head 45.4 and 44.8; but 16 x 2000 tokens 29.5
+// and 33.5, 8 x 4096 28.0 and 29.9, 16 of 500 to 5000 27.5 and 28.6, 4 x 16384
+// with 4 KV heads 28.3 and 33.6, 1 x 8192 13.4 and 14.0.  Shares keep kMinPiece
+// tokens (one tile per wave).
 constexpr long kSmallShare = 2048;
+constexpr long kTinyShare = 512;
 constexpr int kMinPiece = 128;
 // A request split into more than the base slots (see num_slots) keeps shares
 // of this many tokens: 1 x 32768 tokens with 2 KV heads took 21.1 us with 32 or
@@ -509,13 +515,22 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long t
   if (r->split_tokens > 0) {
     W = (total + r->split_tokens - 1) / r->split_tokens;
   } else {
-    // Row-split units (three or four 16-row blocks) also get two workgroups
-    // per CU: each of their tile steps is a barrier-bound chain of LDS and
-    // MFMA latencies, which a second workgroup on the CU overlaps.
-    bool wide = false;
-    for (int b = 0; b < r->B && !wide; ++b) wide = ct.start[b + 1] > ct.start[b] && ct.kind[b] >= ss::kUnitMfma3;
+    // Two workgroups per CU for calls with row-split units, whose every step is
+    // a barrier-bound chain of LDS and MFMA latencies (16 x 32768 tokens with
+    // 64 rows: 341 us a round, 375 with one), and for the short shares above.
+    bool wide = false, valu = false;
+    int requests = 0;
+    for (int b = 0; b < r->B; ++b) {
+      if (ct.start[b + 1] == ct.start[b]) continue;
+      ++requests;
+      wide |= ct.kind[b] >= ss::kUnitMfma3;
+      valu |= ct.kind[b] == ss::kUnitValu;
+    }
     W = std::max<long>(1, kTargetWorkgroups / r->Hkv);
-    if (total / W < kSmallShare || wide) W = std::max<long>(1, 2 * kTargetWorkgroups / r->Hkv);
+    const long share = total / W;
+    const bool many_units = 2 * requests > W || (share < kTinyShare && 4 * requests >= W);
+    if (wide || (share < kSmallShare && (valu || many_units)))
+      W = std::max<long>(1, 2 * kTargetWorkgroups / r->Hkv);
     W = std::min(W, std::max<long>(1, total / kMinPiece));
   }
   W = std::max<long>(1, std::min<long>(W, total));

@@ -2,6 +2,8 @@
 // head) pairs, which have 64 or 128 state slots: every history call of the
 // scenarios covers every token once, writes dense slots below the round's
 // count and stays inside its chunks, through both ways of starting a round.
+// Then the workgroup count of short shares: one per CU, or two where they span
+// requests or run the VALU body.
 #define main plan_check_main
 #include "plan_check.cpp"
 #undef main
@@ -18,6 +20,13 @@ int main() {
     scenario("1 x 400000, 1 KV head", 1, 8, 1, {8}, {400000}, 20000, 0, layout, 20);
     scenario("per-chunk calls", 1, 32, 4, {8}, {100000}, 40000, 0, layout, 1);
     scenario("caller's shares keep 32 slots", 1, 8, 2, {5}, {65536}, 4096, 512, layout, 16, 0, 0, -1, 32);
+    scenario("8 x 4096 (1024 tokens a share)", 8, 32, 8, std::vector<int>(8, 6), std::vector<int>(8, 4096), 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("16 x 1000 (500 tokens a share)", 16, 32, 8, std::vector<int>(16, 6), std::vector<int>(16, 1000), 4096, 0, layout, 1, 0, 0, 0, 64);
+    scenario("16 x 1024 (512 tokens a share)", 16, 32, 8, std::vector<int>(16, 6), std::vector<int>(16, 1024), 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("17 x 2000 (over half the shares span requests)", 17, 32, 8, std::vector<int>(17, 6), std::vector<int>(17, 2000), 4096, 0, layout, 1, 0, 0, 0, 64);
+    scenario("8 x 8191, one row per KV head (VALU)", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8191), 8192, 0, layout, 1, 0, 0, 0, 64);
+    scenario("8 x 8192, one row per KV head", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8192), 8192, 0, layout, 1, 0, 0, 0, 32);
+    scenario("4 x 4096, 64 rows", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 64);
     for (int rep = 0; rep < 60; ++rep) {
       const int hkv = 1 + rng() % 4, B = 1 + rng() % (4 / hkv), G = 1 + rng() % 8;
       std::vector<int> nc(B), h(B);
