@@ -479,7 +479,8 @@ bool plan_tail(const ss_round *r, const CallTokens &ct, long W, long pmax, int m
     }
   }
   plan->num_tail = plan->units() - plan->tail_first;
-  for (int b = 0; b < r->B; ++b) plan->slots_after[b] = std::max(plan->slots_after[b], plan->slot[b]);
+  // from the round's count, not from that of an attempt with finer pieces: finalize merges every slot counted here
+  for (int b = 0; b < r->B; ++b) plan->slots_after[b] = std::max(r->slots_used[b], plan->slot[b]);
   return true;
 }
 

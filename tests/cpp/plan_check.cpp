@@ -2,8 +2,9 @@
 // traversal: every token of every request is visited exactly once per KV
 // head, every buffer resource stays inside its chunk, chains are
 // single-request and single-slot, slots and fresh flags are consistent, the
-// workgroup lists cover every unit once, and every workgroup's share of the
-// call is within one tile of the mean.  The balancing tail's claim loop is
+// workgroup lists cover every unit once, every workgroup's share of the
+// call is within one tile of the mean, and finalize merges exactly the slots
+// that were written.  The balancing tail's claim loop is
 // emulated with the workgroups interleaved at random, from a zero counter
 // (every (tail unit, KV head) pair claimed once, the counter left at zero)
 // and from counters that are not zero (no claim outside the tail's range).
@@ -25,6 +26,7 @@ struct Rec {
   int tail_first, num_tail; uint32_t *claim; int clears_before; int Hkv;
 };
 int g_finalize_launches = 0;
+std::vector<ss::Item> g_finalize_items;   // of the round's finalize
 long g_empty_wgs = 0;             // workgroups launched without a unit of their own
 int g_clear_n = 0;
 std::vector<Rec> g_recs;
@@ -79,7 +81,11 @@ static void rec(const ChunkParams &p, int kind) {
   g_last = &p;
 }
 hipError_t launch_chunk(const ChunkParams &p, hipStream_t) { rec(p, -1); return hipSuccess; }
-hipError_t launch_finalize(const FinalParams &, hipStream_t) { ++g_finalize_launches; return hipSuccess; }
+hipError_t launch_finalize(const FinalParams &p, hipStream_t) {
+  ++g_finalize_launches;
+  g_finalize_items.insert(g_finalize_items.end(), p.items, p.items + p.num_items);
+  return hipSuccess;
+}
 
 hipError_t launch_clear_counters(uint32_t *c, int n, hipStream_t) {
   ++g_clears; g_clear_ptr = c; g_clear_n = n; return hipSuccess;
@@ -323,9 +329,15 @@ static void scenario(const char *name, int B, int Hq, int Hkv, std::vector<int> 
       check_call(B, Hq, Hkv, ncand, part, split, layout, mfma_min_rows, used, r);
     }
     g_finalize_launches = 0;
+    g_finalize_items.clear();
     s = ss_attend_local_candidates(r, (const void *)0x7f2000000000ull, (const void *)0x7f3000000000ull, nullptr);
     if (s == SS_OK) s = ss_round_finalize(r, (float *)0x7f4000000000ull, nullptr, nullptr);
     CHECK(s == SS_OK && g_finalize_launches == 1, "finalize: %s", ss_last_error());
+    // finalize merges the slots that history calls wrote, and no others
+    CHECK((int)g_finalize_items.size() == B, "finalize: %zu items", g_finalize_items.size());
+    for (int b = 0; b < B && b < (int)g_finalize_items.size(); ++b)
+      CHECK(g_finalize_items[b].tok_count == used[b], "%s: finalize merges %d slots of request %d, %d are written", name,
+            g_finalize_items[b].tok_count, b, used[b]);
     ss_round_destroy(r);
     const int want_clears = g_trust_zeroed ? 0 : g_tail_calls > 0 ? 1 : 0;
     CHECK(g_clears == want_clears, "%d clears for %d balanced calls", g_clears, g_tail_calls);
@@ -374,6 +386,8 @@ int main() {
       scenario("config4-like ragged batched 16", 64, 32, 8, n4, h4, 4096, 0, layout, 16, 0, 0, 1);
       scenario("config4-like ragged per-chunk", 64, 32, 8, n4, h4, 4096, 0, layout, 1, 0, 0, -1);
     }
+    // tail pieces of 256 tokens need more units than a launch holds: the tail is cut again with coarser ones
+    scenario("61 x 32000, 32 chunks (tail cut twice)", 61, 32, 8, std::vector<int>(61, 6), std::vector<int>(61, 32000), 1000, 0, layout, 32, 0, 0, 1);
     // row-split units get two workgroups per CU (8 KV heads x 64): 8192-token shares, below the default
     // tail's threshold
     scenario("64q/8kv x 8 candidates (64 rows), batched", 16, 64, 8, std::vector<int>(16, 8), std::vector<int>(16, 32768), 4096, 0, layout, 8, 0, 0, 0, 64);
