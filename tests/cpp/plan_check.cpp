@@ -134,6 +134,18 @@ static std::vector<std::pair<int, int>> emulate_claims(const Rec &rc, uint32_t s
   return got;
 }
 
+// Slots that `bytes` of workspace hold: the states a, m, l of every row and slot, each padded to 256 bytes, and the
+// counter block.
+static int workspace_slots(const std::vector<int> &ncand, int Hq, size_t bytes) {
+  size_t rows = 0;
+  for (int n : ncand) rows += (size_t)n * Hq;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  int slots = 0;
+  for (int s : {32, 64, 128})
+    if (up(s * rows * 512) + 2 * up(s * rows * 4) + 256 <= bytes) slots = s;
+  return slots;
+}
+
 // emulate one history call
 static void check_call(int B, int Hq, int Hkv, const std::vector<int> &ncand, const std::vector<std::vector<int>> &lens,
                        int split, int layout, int mfma_min_rows, std::vector<int> &slots_used, ss_round *r) {
@@ -283,7 +295,9 @@ static void check_call(int B, int Hq, int Hkv, const std::vector<int> &ncand, co
     for (int c = 0; c < nch; ++c)
       for (int t = 0; t < lens[c][b]; ++t) CHECK(cov[b][c][t] == 1, "token b=%d c=%d t=%d visited %d times", b, c, t, cov[b][c][t]);
   for (auto &kv : slot_writes) CHECK(kv.second == 1, "slot (%d,%d) written by %d units", kv.first.first, kv.first.second, kv.second);
-  for (auto &kv : slot_writes) CHECK(kv.first.second < ss::kNumSlots, "slot index");
+  // a round's workspace holds 32 slots, or 64 or 128 for few (request, KV head) pairs; a caller's share size keeps 32
+  const int slots = split > 0 ? 32 : workspace_slots(ncand, Hq, ss_round_workspace_bytes(g_desc));
+  for (auto &kv : slot_writes) CHECK(kv.first.second < slots, "slot %d of %d", kv.first.second, slots);
   for (int b = 0; b < B; ++b) {
     int mx = -1;
     for (auto &kv : slot_writes) if (kv.first.first == b) mx = std::max(mx, kv.first.second);
