@@ -149,17 +149,20 @@ typedef struct {
 /* Bytes of device workspace a round with this descriptor needs (fp32
  * online-softmax states of every query row, per split slot (32 of them; 64 or
  * 128 in rounds of at most 4 (request, KV head) pairs), then a 256-byte
- * counter block whose first word is the balancing tail's claim counter).  0
- * if the descriptor is invalid (see ss_last_error). */
+ * counter block whose first word is the balancing tail's claim counter).  A
+ * round of so few pairs also runs, somewhat slower, on a workspace of 64 or 32
+ * slots, so the workspace of a larger cohort serves every smaller one of the
+ * same heads; one that is less than a slot's states short of the bytes returned
+ * here is refused.  0 if the descriptor is invalid (see ss_last_error). */
 size_t ss_round_workspace_bytes(const ss_round_desc *desc);
 
 /* Start a round (paper Sec. 4.2: state (m, l, a) = (-inf, 0, 0) per query and
  * head).  q: device bf16 [sum n_b, Hq, d], read by the later calls, so it
  * must stay unchanged until ss_round_finalize's work has completed.
- * workspace: device, 256-byte aligned, >= ss_round_workspace_bytes(desc);
- * owned by the round until finalize's work has completed.  The empty state
- * is tracked on the host (a split slot is written before it is ever read),
- * so this call enqueues nothing on `stream`; unless desc->counters_zeroed is
+ * workspace: device, 256-byte aligned, >= ss_round_workspace_bytes(desc) (or
+ * enough for fewer slots, see there); owned by the round
+ * until finalize's work has completed.  The empty state is tracked on the
+ * host (a split slot is written before it is ever read), so this call enqueues nothing on `stream`; unless desc->counters_zeroed is
  * set, the round's first history call with a balancing tail enqueues a
  * one-wave kernel that zeroes the counter block before its attention
  * launch.

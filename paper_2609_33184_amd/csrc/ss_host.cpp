@@ -158,7 +158,8 @@ ss_status validate_desc(const ss_round_desc *d) {
 // 1 x 131072 tokens, 32q/4kv 77.8 -> 54.1 us, 8q/2kv 55.7 -> 31.0 us; 1 x 32768,
 // 32q/4kv, 6 candidates 27.2 -> 21.3 us, 4 candidates 21.4 -> 19.7 us.  More
 // slots where the CUs are full only lengthen finalize: 1 x 32768, 32q/8kv 28.6
-// us with 32, 30.4 us with 64.
+// us with 32, 30.4 us with 64.  More slots than 32 are only ever a matter of
+// speed: a round takes as many as its workspace holds (workspace_slots).
 long num_slots(long B, long Hkv) {
   const long pairs = B * Hkv;
   return pairs > 4 ? ss::kBaseSlots : pairs > 2 ? 2 * ss::kBaseSlots : ss::kNumSlots;
@@ -168,8 +169,8 @@ long num_slots(long B, long Hkv) {
 // words (the first is the balancing tail's claim counter).
 struct WorkspaceLayout {
   size_t m, l, counters, bytes;   // offsets (a is at 0) and the whole size
-  WorkspaceLayout(long R, long B, long Hkv) {
-    const size_t rows = (size_t)num_slots(B, Hkv) * R;
+  WorkspaceLayout(long R, long slots) {
+    const size_t rows = (size_t)slots * R;
     m = align_up(rows * ss::kHeadDim * sizeof(float), 256);
     l = m + align_up(rows * sizeof(float), 256);
     counters = l + align_up(rows * sizeof(float), 256);
@@ -177,12 +178,28 @@ struct WorkspaceLayout {
   }
 };
 
+// Slots of a round on a workspace of `bytes`: num_slots, or half or a quarter
+// of that in a smaller workspace, but never below the base slots.  A loop that
+// allocates for its largest cohort can so run its smaller ones, which may ask
+// for more (16q/2kv with 8 candidates: 3 requests 6.4 MB, 2 requests 8.5 MB).
+// Less than one slot short of the whole is a miscount and stays refused: cohorts
+// of the same heads differ by at least 32 Hq rows of states, and a slot of a
+// round of few pairs has at most 32 candidates, so at most that many.
+long workspace_slots(long R, long B, long Hkv, size_t bytes) {
+  long slots = num_slots(B, Hkv);
+  const size_t whole = WorkspaceLayout(R, slots).bytes;
+  if (bytes < whole && whole - bytes < (size_t)R * ss::kHeadDim * sizeof(float)) return slots;
+  while (slots > ss::kBaseSlots && WorkspaceLayout(R, slots).bytes > bytes) slots /= 2;
+  return slots;
+}
+
 }  // namespace
 
 struct ss_round {
   int32_t B, Hq, Hkv, G;
   float scale;
   int32_t max_chunk_tokens, split_tokens, mfma_min_rows, kv_layout, tail_permille;
+  int32_t slots = ss::kBaseSlots;    // state slots per query row that the workspace holds
   std::vector<int32_t> n_cand, row_off;
   uint32_t *counters = nullptr;      // the workspace's counter block (kClaimCounters words)
   bool counters_ready = false;       // the block is known to be zero (cleared, or the caller said so)
@@ -539,10 +556,9 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long t
   // Past the base slots only while the shares keep kMinManyShare tokens.
   int max_slots = ss::kBaseSlots;
   if (r->split_tokens == 0) {
-    const long slots = num_slots(r->B, r->Hkv);
-    const long many = std::min({kTargetWorkgroups / r->Hkv, total / kMinManyShare, slots * r->B});
-    if (slots > ss::kBaseSlots && many > ss::kBaseSlots) {
-      max_slots = (int)slots;
+    const long many = std::min({kTargetWorkgroups / r->Hkv, total / kMinManyShare, (long)r->slots * r->B});
+    if (r->slots > ss::kBaseSlots && many > ss::kBaseSlots) {
+      max_slots = r->slots;
       W = many;
     }
   }
@@ -879,7 +895,7 @@ size_t ss_round_workspace_bytes(const ss_round_desc *desc) {
   if (validate_desc(desc) != SS_OK) return 0;
   long R = 0;
   for (int b = 0; b < desc->num_requests; ++b) R += (long)desc->num_cand[b] * desc->num_q_heads;
-  return WorkspaceLayout(R, desc->num_requests, desc->num_kv_heads).bytes;
+  return WorkspaceLayout(R, num_slots(desc->num_requests, desc->num_kv_heads)).bytes;
 }
 
 }  // extern "C"
@@ -898,7 +914,8 @@ ss_status init_round(ss_round **out, const ss_round_desc *desc, const void *q, v
   if (q == nullptr || !aligned(q, 16)) return fail(SS_ERR_INVALID_ARGUMENT, "q must be non-null and 16-byte aligned");
   long R = 0;
   for (int b = 0; b < desc->num_requests; ++b) R += (long)desc->num_cand[b] * desc->num_q_heads;
-  const WorkspaceLayout layout(R, desc->num_requests, desc->num_kv_heads);
+  const long slots = workspace_slots(R, desc->num_requests, desc->num_kv_heads, workspace_bytes);
+  const WorkspaceLayout layout(R, slots);
   const size_t need = layout.bytes;
   if (workspace == nullptr || !aligned(workspace, 256))
     return fail(SS_ERR_WORKSPACE, "workspace must be non-null and 256-byte aligned");
@@ -910,6 +927,7 @@ ss_status init_round(ss_round **out, const ss_round_desc *desc, const void *q, v
   r->B = desc->num_requests;
   r->Hq = desc->num_q_heads;
   r->Hkv = desc->num_kv_heads;
+  r->slots = (int32_t)slots;
   r->G = r->Hq / r->Hkv;
   r->scale = desc->softmax_scale;
   r->max_chunk_tokens = desc->max_chunk_tokens;

@@ -96,6 +96,8 @@ hipError_t scratch_address(void **p) { *p = (void *)0x7f1000000000ull; return hi
 }
 
 static const ss_round_desc *g_desc = nullptr;
+static size_t g_ws_bytes = 0;         // the caller's workspace in bytes; 0 = what the round asks for
+static size_t workspace_bytes() { return g_ws_bytes ? g_ws_bytes : ss_round_workspace_bytes(g_desc); }
 static bool g_trust_zeroed = false;   // the round may skip the counter clear
 static int g_tail_calls = 0;
 static std::mt19937 g_emu(11);
@@ -296,7 +298,7 @@ static void check_call(int B, int Hq, int Hkv, const std::vector<int> &ncand, co
       for (int t = 0; t < lens[c][b]; ++t) CHECK(cov[b][c][t] == 1, "token b=%d c=%d t=%d visited %d times", b, c, t, cov[b][c][t]);
   for (auto &kv : slot_writes) CHECK(kv.second == 1, "slot (%d,%d) written by %d units", kv.first.first, kv.first.second, kv.second);
   // a round's workspace holds 32 slots, or 64 or 128 for few (request, KV head) pairs; a caller's share size keeps 32
-  const int slots = split > 0 ? 32 : workspace_slots(ncand, Hq, ss_round_workspace_bytes(g_desc));
+  const int slots = split > 0 ? 32 : workspace_slots(ncand, Hq, workspace_bytes());
   for (auto &kv : slot_writes) CHECK(kv.first.second < slots, "slot %d of %d", kv.first.second, slots);
   for (int b = 0; b < B; ++b) {
     int mx = -1;
@@ -324,9 +326,10 @@ static void scenario(const char *name, int B, int Hq, int Hkv, std::vector<int> 
     d.balance_permille = balance;
     d.counters_zeroed = mode >= 1;
     g_trust_zeroed = mode == 1;
+    if (mode == 2 && g_ws_bytes) continue;   // about the caller's workspace
     g_desc = &d; g_clears = 0; g_clear_ptr = nullptr; g_tail_calls = 0;
     ss_round *r = nullptr;
-    size_t ws = ss_round_workspace_bytes(&d);
+    size_t ws = workspace_bytes();
     if (mode == 2 && ws > ss::kScratchBytes) {
       CHECK(ss_round_init_scratch(&r, &d, (const void *)0x7f0000000000ull, nullptr) == SS_ERR_WORKSPACE && r == nullptr,
             "%s: a round beyond the scratch was accepted", name);

@@ -27,6 +27,22 @@ int main() {
     scenario("8 x 8191, one row per KV head (VALU)", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8191), 8192, 0, layout, 1, 0, 0, 0, 64);
     scenario("8 x 8192, one row per KV head", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8192), 8192, 0, layout, 1, 0, 0, 0, 32);
     scenario("4 x 4096, 64 rows", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 64);
+    // A workspace allocated for a larger cohort serves a smaller one, which asks for more slots than it holds.
+    auto bytes_of = [](int B, int Hq, int Hkv, int n) {
+      const std::vector<int> nc(B, n);
+      ss_round_desc d{};
+      d.num_requests = B; d.num_q_heads = Hq; d.num_kv_heads = Hkv; d.head_dim = 128; d.softmax_scale = 0.088f;
+      d.num_cand = nc.data(); d.max_chunk_tokens = 1;
+      return ss_round_workspace_bytes(&d);
+    };
+    g_ws_bytes = bytes_of(3, 16, 2, 8);
+    CHECK(g_ws_bytes < bytes_of(2, 16, 2, 8) && g_ws_bytes < bytes_of(1, 16, 2, 8), "the smaller cohorts ask for more");
+    scenario("2 x 65536, workspace of 3 requests (32 slots)", 2, 16, 2, {8, 8}, {65536, 65536}, 8192, 0, layout, 8, 0, 0, -1);
+    scenario("1 x 65536, workspace of 3 requests (64 slots)", 1, 16, 2, {8}, {65536}, 8192, 0, layout, 8, 0, 0, 0, 64);
+    scenario("1 x 65536 by chunk, workspace of 3 requests", 1, 16, 2, {8}, {65536}, 32768, 0, layout, 1);
+    g_ws_bytes = bytes_of(5, 16, 2, 8);
+    scenario("1 x 65536, workspace of 5 requests (128 slots)", 1, 16, 2, {8}, {65536}, 8192, 0, layout, 8, 0, 0, 0, 128);
+    g_ws_bytes = 0;
     for (int rep = 0; rep < 60; ++rep) {
       const int hkv = 1 + rng() % 4, B = 1 + rng() % (4 / hkv), G = 1 + rng() % 8;
       std::vector<int> nc(B), h(B);

@@ -75,6 +75,54 @@ def test_many_slots(heads, lens, cands, chunk, batch, scratch):
     assert_parity(b.lse.double().cpu().numpy(), ref_l, "lse", max_abs=1e-4, rel_l2=1e-5)
 
 
+def test_workspace_of_a_larger_cohort():
+    """Fewer requests may ask for more slots, and run on what the larger cohort's workspace holds."""
+    heads = (16, 2)
+    need = lambda n: ss.ss_round_workspace_bytes(ss.make_desc([8] * n, *heads))
+    held = need(3)
+    assert held < need(2) == 64 * 256 * 520 + 256 and held < need(1) == 128 * 128 * 520 + 256
+    for n in (3, 2, 1):
+        ss.ss_round_destroy(ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, held))
+        base = 32 * 128 * n * 520 + 256          # 32 slots: the least that a round takes
+        ss.ss_round_destroy(ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, base))
+        for short in (base - 1, need(n) - 1, need(n) - 256):
+            with pytest.raises(ss.SpecStreamError) as e:
+                ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, short)
+            assert e.value.status == ss.SS_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("heads", [(1, 1), (2, 2), (3, 3), (4, 4), (15, 3), (16, 2), (64, 1), (32, 4)])
+def test_every_larger_cohorts_workspace_serves(heads):
+    """Any cohort runs on the workspace of any cohort of the same heads with as many candidates or more."""
+    need = lambda cand: ss.ss_round_workspace_bytes(ss.make_desc(cand, *heads))
+    cohorts = [[n] * b for b in (1, 2, 3, 4, 5, 8) for n in (1, 3, 5, 8) if n * heads[0] // heads[1] <= 64]
+    for small in cohorts:
+        for large in cohorts:
+            if len(large) >= len(small) and sum(large) >= sum(small):
+                ss.ss_round_destroy(ss.ss_round_init(ss.make_desc(small, *heads), 0x7f0000000000, 0x7f1000000000, need(large)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("slots", [32, 64])
+def test_fewer_slots_than_asked_for(slots):
+    """1 x 40000 tokens, 2 KV heads: 78 shares with 128 slots, 64 or 32 on smaller workspaces."""
+    w = W.custom([40000], [7], num_q_heads=6, num_kv_heads=2, chunk_tokens=8192, seed_base=78)
+    b = H.RoundBuffers(w)
+    up = lambda x: (x + 255) // 256 * 256
+    b.ws_bytes = up(42 * slots * 512) + 2 * up(42 * slots * 4) + 256
+    b.ws = torch.full((b.ws_bytes + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN states
+    b.out.fill_(float("nan"))
+    chunks = H.hbm_history(w)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    H.run_round(b, chunks, s.cuda_stream, batch=5)
+    s.synchronize()
+    assert bool((b.ws[b.ws_bytes:] == 0xFF).all())
+    ref_o, ref_l = _oracle(w)
+    assert_parity(b.out.double().cpu().numpy(), ref_o, f"{slots} slots", rel_l2=1e-5)
+    assert_parity(b.lse.double().cpu().numpy(), ref_l, "lse", max_abs=1e-4, rel_l2=1e-5)
+
+
 _CACHE = {}
 
 
