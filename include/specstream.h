@@ -130,8 +130,9 @@ typedef struct {
                                allocated and has since been written only by
                                rounds of this library whose work completed
                                without error (a serving loop reusing one
-                               workspace), so no clear is enqueued.  A block
-                               that is not zero when promised gives wrong
+                               workspace, given with the same workspace_bytes
+                               to all its rounds), so no clear is enqueued.  A
+                               block that is not zero when promised gives wrong
                                results (never an access outside the
                                workspace).                                    */
 } ss_round_desc;
@@ -148,24 +149,25 @@ typedef struct {
 
 /* Bytes of device workspace a round with this descriptor needs (fp32
  * online-softmax states of every query row, per split slot (32 of them; 64 or
- * 128 in rounds of at most 4 (request, KV head) pairs), then a 256-byte
- * counter block whose first word is the balancing tail's claim counter).  A
- * round of so few pairs also runs, somewhat slower, on a workspace of 64 or 32
- * slots, so the workspace of a larger cohort serves every smaller one of the
- * same heads; one that is less than a slot's states short of the bytes returned
- * here is refused.  0 if the descriptor is invalid (see ss_last_error). */
+ * 128 in rounds of at most 4 (request, KV head) pairs), and a 256-byte counter
+ * block whose first word is the balancing tail's claim counter, in the last
+ * whole 256 bytes of the workspace given to ss_round_init).  A round of so few
+ * pairs also runs, somewhat slower, on a workspace of 64 or 32 slots, so the
+ * workspace of a larger cohort serves every smaller one of the same heads; one
+ * that is less than a slot's states short of the bytes returned here is
+ * refused.  0 if the descriptor is invalid (see ss_last_error). */
 size_t ss_round_workspace_bytes(const ss_round_desc *desc);
 
 /* Start a round (paper Sec. 4.2: state (m, l, a) = (-inf, 0, 0) per query and
  * head).  q: device bf16 [sum n_b, Hq, d], read by the later calls, so it
  * must stay unchanged until ss_round_finalize's work has completed.
  * workspace: device, 256-byte aligned, >= ss_round_workspace_bytes(desc) (or
- * enough for fewer slots, see there); owned by the round
- * until finalize's work has completed.  The empty state is tracked on the
- * host (a split slot is written before it is ever read), so this call enqueues nothing on `stream`; unless desc->counters_zeroed is
- * set, the round's first history call with a balancing tail enqueues a
- * one-wave kernel that zeroes the counter block before its attention
- * launch.
+ * enough for fewer slots, see there); owned by the round until finalize's work
+ * has completed.  The empty state is tracked on the host (a split slot is
+ * written before it is ever read), so this call enqueues nothing on `stream`;
+ * unless desc->counters_zeroed is set, the round's first history call with a
+ * balancing tail enqueues a one-wave kernel that zeroes the counter block
+ * before its attention launch.
  * On success *out receives a new handle (free with ss_round_destroy). */
 ss_status ss_round_init(ss_round **out, const ss_round_desc *desc, const void *q,
                         void *workspace, size_t workspace_bytes, hipStream_t stream);

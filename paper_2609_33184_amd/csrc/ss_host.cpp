@@ -166,15 +166,17 @@ long num_slots(long B, long Hkv) {
 }
 
 // Workspace: slot states a, m, l, then the counter block of kClaimCounters
-// words (the first is the balancing tail's claim counter).
+// words (the first is the balancing tail's claim counter).  The block takes the
+// last bytes of what the caller gives, behind the states of every round that
+// fits, so that it stays zero while rounds of other sizes use the workspace.
 struct WorkspaceLayout {
-  size_t m, l, counters, bytes;   // offsets (a is at 0) and the whole size
+  static constexpr size_t kCounterBytes = (ss::kClaimCounters * sizeof(uint32_t) + 255) / 256 * 256;
+  size_t m, l, bytes;   // offsets (a is at 0) and the whole size
   WorkspaceLayout(long R, long slots) {
     const size_t rows = (size_t)slots * R;
     m = align_up(rows * ss::kHeadDim * sizeof(float), 256);
     l = m + align_up(rows * sizeof(float), 256);
-    counters = l + align_up(rows * sizeof(float), 256);
-    bytes = counters + align_up(ss::kClaimCounters * sizeof(uint32_t), 256);
+    bytes = l + align_up(rows * sizeof(float), 256) + kCounterBytes;
   }
 };
 
@@ -951,7 +953,7 @@ ss_status init_round(ss_round **out, const ss_round_desc *desc, const void *q, v
   r->st.a = reinterpret_cast<float *>(ws);
   r->st.m = reinterpret_cast<float *>(ws + layout.m);
   r->st.l = reinterpret_cast<float *>(ws + layout.l);
-  r->counters = reinterpret_cast<uint32_t *>(ws + layout.counters);
+  r->counters = reinterpret_cast<uint32_t *>(ws + workspace_bytes / 256 * 256 - WorkspaceLayout::kCounterBytes);
   r->counters_ready = desc->counters_zeroed != 0;
   r->tail_permille = desc->balance_permille;
   r->st.R = (int32_t)R;
@@ -1028,7 +1030,7 @@ ss_status ss_round_init_scratch(ss_round **out, const ss_round_desc *desc, const
   void *scratch = nullptr;
   const hipError_t e = ss::scratch_address(&scratch);
   if (e != hipSuccess) return hip_fail(e, "scratch address lookup");
-  const ss_status st = init_round(out, desc, q, scratch, ss::kScratchBytes);
+  const ss_status st = init_round(out, desc, q, scratch, need);
   // The counter block sits at the end of this round's share of the scratch,
   // where an earlier round of another size may have left state: always clear.
   if (st == SS_OK) (*out)->counters_ready = false;

@@ -191,9 +191,10 @@ static void check_call(int B, int Hq, int Hkv, const std::vector<int> &ncand, co
     }
   }
   if (total >= 32 * wgs) CHECK(max_share <= (total + wgs - 1) / wgs + 31, "share %ld > mean %ld + a tile", max_share, total / wgs);
-  // counter block: at the workspace's end, cleared once per round (before
-  // the first launch that uses it) unless the caller said it is zero
-  const size_t ws_end = 0x7f1000000000ull + ss_round_workspace_bytes(g_desc);
+  // counter block: at the workspace's end, so in the same place for every
+  // round on it; cleared once per round (before the first launch that uses
+  // it) unless the caller said it is zero
+  const size_t ws_end = 0x7f1000000000ull + workspace_bytes() / 256 * 256;
   const size_t block_words = ss::kClaimCounters;
   const uintptr_t block = ws_end - (block_words * 4 + 255) / 256 * 256;
   for (auto &rc : g_recs) {

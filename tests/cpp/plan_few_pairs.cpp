@@ -42,6 +42,12 @@ int main() {
     scenario("1 x 65536 by chunk, workspace of 3 requests", 1, 16, 2, {8}, {65536}, 32768, 0, layout, 1);
     g_ws_bytes = bytes_of(5, 16, 2, 8);
     scenario("1 x 65536, workspace of 5 requests (128 slots)", 1, 16, 2, {8}, {65536}, 8192, 0, layout, 8, 0, 0, 0, 128);
+    // One zero-filled workspace serves cohorts of other sizes and slot counts in turn: the counter block stays where
+    // it is, outside every round's states (the calls have a balancing tail).
+    g_ws_bytes = bytes_of(40, 32, 4, 4) + 100;
+    scenario("16 x 65536, workspace of 40 requests", 16, 32, 4, std::vector<int>(16, 3), std::vector<int>(16, 65536), 4096, 0, layout, 32, 0, 0, 1);
+    scenario("40 x 40000, workspace of 40 requests", 40, 32, 4, std::vector<int>(40, 4), std::vector<int>(40, 40000), 4096, 0, layout, 32, 0, 0, 1);
+    scenario("5 x 400000, workspace of 40 requests", 5, 32, 4, {4, 1, 2, 3, 4}, std::vector<int>(5, 400000), 16384, 0, layout, 32, 0, 0, 1);
     g_ws_bytes = 0;
     for (int rep = 0; rep < 60; ++rep) {
       const int hkv = 1 + rng() % 4, B = 1 + rng() % (4 / hkv), G = 1 + rng() % 8;

@@ -123,6 +123,34 @@ def test_fewer_slots_than_asked_for(slots):
     assert_parity(b.lse.double().cpu().numpy(), ref_l, "lse", max_abs=1e-4, rel_l2=1e-5)
 
 
+@pytest.mark.gpu
+def test_one_zeroed_workspace_for_every_cohort():
+    """Cohorts of other sizes and slot counts take turns on one zero-filled workspace; their claim counter stays
+    zero, so balanced rounds equal, bitwise, the same rounds on workspaces of their own."""
+    cohorts = [W.custom(lens, cands, num_q_heads=8, num_kv_heads=2, chunk_tokens=65536, seed_base=79)
+               for lens, cands in [([200000] * 3, [8] * 3), ([300000, 262144], [5, 2]), ([262144] * 4, [8, 1, 2, 3])]]
+    s = torch.cuda.Stream()
+    rounds = []
+    for w in cohorts:
+        chunks = H.hbm_history(w)
+        b = H.RoundBuffers(w, balance_permille=100)
+        torch.cuda.synchronize()
+        H.run_round(b, chunks, s.cuda_stream, batch=8)
+        s.synchronize()
+        rounds.append((w, chunks, b.out.clone(), b.lse.clone(), b.ws_bytes))
+    held = torch.zeros(max(r[4] for r in rounds) + 1000, dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        for w, chunks, out, lse, _ in rounds:
+            b = H.RoundBuffers(w, balance_permille=100, counters_zeroed=1)
+            b.ws, b.ws_bytes = held, held.numel()
+            torch.cuda.synchronize()
+            H.run_round(b, chunks, s.cuda_stream, batch=8)
+            s.synchronize()
+            assert torch.equal(b.out, out) and torch.equal(b.lse, lse), f"{w.B} requests"
+            counters = held[held.numel() // 256 * 256 - 256:][:256]
+            assert not bool(counters.any())
+
+
 _CACHE = {}
 
 
