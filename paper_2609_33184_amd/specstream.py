@@ -148,14 +148,18 @@ def _lens(len_: Sequence[int]):
     return (ctypes.c_int32 * len(len_))(*[int(x) for x in len_])
 
 
-def _counts(values: Iterable[int], fallback) -> array:
-    """Token counts as a C int array, filled without a Python object per count;
-    values that only int() takes (and counts beyond 32 bits, which the library
-    refuses) go through ``fallback()``, their list."""
+def _counts(values: Iterable[int], where: str) -> array:
+    """Token counts as a C int array.  The values are read once, so they may
+    come from an iterator; those that only int() takes go through it.  Counts
+    beyond 32 bits are refused, as the library cannot see them."""
+    counts = list(values)
     try:
-        return array("i", iter(values))
-    except (TypeError, OverflowError):
-        return array("i", bytes((ctypes.c_int32 * len(fb))(*[int(x) for x in fb])) if (fb := fallback()) else b"")
+        try:
+            return array("i", counts)
+        except TypeError:
+            return array("i", [int(x) for x in counts])
+    except OverflowError:
+        raise SpecStreamError(SS_ERR_INVALID_ARGUMENT, where, "a token count is beyond 32 bits") from None
 
 
 # ---------------------------------------------------------------------------
@@ -188,7 +192,7 @@ def ss_upload_chunk(dst_device: int, src_pinned_host: int, nbytes: int, copy_str
 
 def ss_attend_history_chunk(r: int, k: int, v: int, len_: Sequence[int], wait_before: Optional[int] = None,
                             signal_after: Optional[int] = None, stream: int = 0) -> None:
-    a = _counts(len_, lambda: list(len_))
+    a = _counts(len_, "ss_attend_history_chunk")
     _check(load().ss_attend_history_chunk(r, k, v, a.buffer_info()[0], wait_before, signal_after, stream),
            "ss_attend_history_chunk")
 
@@ -199,7 +203,7 @@ def ss_attend_history_chunks(r: int, k: Sequence[int], v: Sequence[int], lens: S
     n = len(k)
     kp = (ctypes.c_void_p * n)(*k)
     vp = (ctypes.c_void_p * n)(*v)
-    a = _counts(chain.from_iterable(lens), lambda: [x for row in lens for x in row])
+    a = _counts(chain.from_iterable(lens), "ss_attend_history_chunks")
     _check(load().ss_attend_history_chunks(r, n, kp, vp, a.buffer_info()[0], wait_before, signal_after, stream),
            "ss_attend_history_chunks")
 
@@ -234,12 +238,12 @@ def ss_pipeline_create(staging0: int, staging1: int, slot_bytes: int, copy_strea
 
 
 def ss_pipeline_attend_chunk(p: int, r: int, host_kv: int, len_: Sequence[int], stream: int = 0) -> None:
-    a = _counts(len_, lambda: list(len_))
+    a = _counts(len_, "ss_pipeline_attend_chunk")
     _check(load().ss_pipeline_attend_chunk(p, r, host_kv, a.buffer_info()[0], stream), "ss_pipeline_attend_chunk")
 
 
 def ss_pipeline_attend_chunks(p: int, r: int, host_kv: int, lens: Sequence[Sequence[int]], stream: int = 0) -> None:
-    a = _counts(chain.from_iterable(lens), lambda: [x for row in lens for x in row])
+    a = _counts(chain.from_iterable(lens), "ss_pipeline_attend_chunks")
     _check(load().ss_pipeline_attend_chunks(p, r, len(lens), host_kv, a.buffer_info()[0], stream),
            "ss_pipeline_attend_chunks")
 
