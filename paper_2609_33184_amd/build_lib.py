@@ -35,7 +35,7 @@ def build(verbose: bool = True) -> str:
         kobj = os.path.join(bdir, name + ".o")
         _run([HIPCC, *COMMON, *DEVICE_ONLY, "-c", os.path.join(CSRC, name + ".hip"), "-o", kobj])
         objs.append(kobj)
-    for name in ("ss_host", "ss_tier", "ss_width"):
+    for name in ("ss_host", "ss_upload", "ss_tier", "ss_width"):
         hobj = os.path.join(bdir, name + ".o")
         _run([HIPCC, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",
               os.path.join(CSRC, name + ".cpp"), "-o", hobj])

@@ -12,8 +12,6 @@
 
 #include "ss_kernels.h"
 
-#include <cstring>
-
 namespace ss {
 namespace {
 
@@ -25,8 +23,6 @@ constexpr int kCopyDepth = 4;      // 16-byte loads in flight per thread
 // only queue up in front of it (the streamed round above: 1252 us with 16, 1280
 // with 32, 1283 with 64, 1344 with 128) and take CUs from the attention.
 constexpr unsigned kCopyWgs = 16;
-// Larger uploads gain nothing and leave the CUs to others.
-constexpr uint64_t kMaxUpload = uint64_t(64) << 20;
 
 __global__ void __launch_bounds__(kCopyThreads) copy_kernel(const u32x4_t *src, u32x4_t *dst, uint64_t n, uint32_t tail) {
   constexpr uint64_t kBlock = (uint64_t)kCopyThreads * kCopyDepth;
@@ -55,33 +51,6 @@ hipError_t launch_upload(void *dst, const void *mapped_src, uint64_t bytes, hipS
   hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyThreads), 0, s, static_cast<const u32x4_t *>(mapped_src),
                      static_cast<u32x4_t *>(dst), n, (uint32_t)(bytes % 16));
   return hipGetLastError();
-}
-
-const void *upload_source(const void *dst, const void *src, uint64_t bytes, hipStream_t s) {
-  if (bytes > kMaxUpload) return nullptr;
-  // a range's device address, if both its ends are memory of the wanted type
-  // and as far apart as they should be
-  auto mapped = [&](const void *p, hipMemoryType type, int device) -> const void * {
-    hipPointerAttribute_t first, last;
-    std::memset(&first, 0, sizeof first);
-    std::memset(&last, 0, sizeof last);
-    if (hipPointerGetAttributes(&first, p) != hipSuccess ||
-        hipPointerGetAttributes(&last, static_cast<const char *>(p) + bytes - 1) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    const char *d = static_cast<const char *>(first.devicePointer);
-    const bool whole = d != nullptr && first.type == type && last.type == type && first.device == device &&
-                       last.device == device && last.devicePointer == d + bytes - 1;
-    return whole && reinterpret_cast<uintptr_t>(d) % 16 == 0 ? d : nullptr;
-  };
-  int current = -1;
-  hipDevice_t of_stream = -1;
-  if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &of_stream) != hipSuccess || of_stream != current) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  return mapped(dst, hipMemoryTypeDevice, current) == dst ? mapped(src, hipMemoryTypeHost, current) : nullptr;
 }
 
 }  // namespace ss
