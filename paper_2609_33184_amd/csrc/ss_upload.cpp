@@ -10,6 +10,10 @@ namespace {
 // Larger uploads gain nothing and leave the CUs to others.
 constexpr uint64_t kMaxUpload = uint64_t(64) << 20;
 
+// Non-coherent pinned memory may stay in the GPU's caches from one kernel to the
+// next, so that a kernel could read what the host has replaced since.
+constexpr unsigned kNonCoherent = hipHostMallocNonCoherent | hipExtHostRegisterCoarseGrained;
+
 // The address at which GPU `device` sees [p, p + bytes), if the range lies
 // inside one allocation of the wanted type there and is 16-byte aligned; else
 // null.  Neighbouring addresses prove nothing: a range over two allocations
@@ -28,6 +32,7 @@ const void *mapped(const void *p, uint64_t bytes, hipMemoryType type, int device
     return nullptr;
   }
   const uintptr_t d = reinterpret_cast<uintptr_t>(attr.devicePointer), s = reinterpret_cast<uintptr_t>(start);
+  if (type == hipMemoryTypeHost && (attr.allocationFlags & kNonCoherent) != 0) return nullptr;
   const bool whole = d != 0 && d >= s && d - s <= size && bytes <= size - (d - s);
   return whole && attr.type == type && attr.device == device && d % 16 == 0 ? attr.devicePointer : nullptr;
 }

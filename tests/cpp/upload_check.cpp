@@ -135,6 +135,9 @@ int main() {
   fail_engine = 1;
   expect("refused by the copy call", 'e', way(D1, H0 + 10 * M, 8 * MT, SS_ERR_HIP));
   fail_engine = 0;
+  // memory that the GPU may cache is the copy engine's: a kernel could read what an earlier one left in the cache
+  expect("non-coherent source", 'e', way(D1, H1 + 512 * M, MT));
+  expect("explicitly coherent source", 'k', way(D1, H1 + 768 * M, MT));
   expect("source 8 bytes off", 'e', way(D1, H1 + 8, MT));
   expect("pinned for another GPU", 'e', way(D1, H1 + 256 * M, MT));
   expect("slot on another GPU", 'e', way(D1 + 256 * M, H1, MT));
