@@ -179,9 +179,8 @@ ss_status ss_round_init(ss_round **out, const ss_round_desc *desc, const void *q
  * slot's "free" event); if signal_after is non-null it is recorded on
  * copy_stream after the copy (the slot's "ready" event).  src must be
  * page-locked host memory (hipHostMalloc / pinned tensors), else
- * SS_ERR_NOT_PINNED; dst must be device memory.  bytes > 0.  Up to 64 MiB
- * between 16-byte-aligned addresses the copy is a kernel of 16 workgroups on
- * copy_stream (the pipeline's uploads too), otherwise the copy engine's. */
+ * SS_ERR_NOT_PINNED; dst must be device memory.  bytes > 0.  The copy engine
+ * does the copy, beside whatever runs on the GPU. */
 ss_status ss_upload_chunk(void *dst_device, const void *src_pinned_host, size_t bytes,
                           hipStream_t copy_stream, hipEvent_t wait_before, hipEvent_t signal_after);
 
@@ -246,7 +245,11 @@ ss_status ss_pipeline_create(ss_pipeline **out, void *staging0, void *staging1, 
  * (SS_KV_HEAD_MAJOR_KV: the chunk's one [Hkv][sum_b len_b][2][d] buffer);
  * len as in ss_attend_history_chunk.  The chunk may belong
  * to any round (e.g. the next layer), so transfers run ahead across layer
- * boundaries. */
+ * boundaries.  Uploads of at most 8 MiB, from a 16-byte-aligned address inside
+ * one coherent allocation of the copy stream's GPU, are a kernel of at most 16
+ * workgroups on copy_stream, which starts sooner than the copy engine; larger
+ * ones are the copy engine's.  Beside work that fills the GPU for long, larger
+ * chunks, transfer batches or ss_upload_chunk keep uploads off the CUs. */
 ss_status ss_pipeline_attend_chunk(ss_pipeline *p, ss_round *r, const void *host_kv,
                                    const int32_t *len, hipStream_t stream);
 

@@ -851,18 +851,19 @@ ss_status check_copy(const void *dst, const void *src, size_t bytes, hipMemcpyKi
   return SS_OK;
 }
 
-// Enqueue a checked copy on copy_stream: wait for wait_before, copy, record
-// signal_after.  *enqueued (nullable) tells whether any of it reached the
+// Enqueue a checked copy on copy_stream: wait for wait_before, copy (small
+// uploads of the pipeline by a kernel, see upload_source), record signal_after.
+// *enqueued (null outside the pipeline) tells whether any of it reached the
 // stream before an error.
 ss_status enqueue_copy(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t copy_stream,
                        hipEvent_t wait_before, hipEvent_t signal_after, bool *enqueued) {
+  const bool pipelined = enqueued != nullptr;
   if (enqueued != nullptr) *enqueued = false;
   hipError_t e;
   if (wait_before != nullptr && (e = hipStreamWaitEvent(copy_stream, wait_before, 0)) != hipSuccess)
     return hip_fail(e, "hipStreamWaitEvent (copy)");
   if (enqueued != nullptr) *enqueued = wait_before != nullptr;
-  const void *mapped =
-      kind == hipMemcpyHostToDevice && ss::upload_source != nullptr ? ss::upload_source(dst, src, bytes, copy_stream) : nullptr;
+  const void *mapped = pipelined && ss::upload_source != nullptr ? ss::upload_source(dst, src, bytes, copy_stream) : nullptr;
   if (mapped != nullptr) {
     if ((e = ss::launch_upload(dst, mapped, bytes, copy_stream)) != hipSuccess) return hip_fail(e, "upload kernel launch");
   } else if ((e = hipMemcpyAsync(dst, src, bytes, kind, copy_stream)) != hipSuccess) {

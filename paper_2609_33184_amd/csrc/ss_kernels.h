@@ -159,8 +159,9 @@ hipError_t launch_clear_counters(uint32_t *counters, int n, hipStream_t s);
 
 // Upload by kernel.  upload_source: the address at which the GPU that `s`
 // belongs to sees the pinned range [src, src + bytes), if the range and dst's
-// lie each inside one of its allocations and are 16-byte aligned; null if the
-// copy engine has to do the upload.  launch_upload copies from such an address.
+// lie each inside one of its allocations, are 16-byte aligned, whole 16-byte
+// words and small enough; null if the copy engine has to do the upload.
+// launch_upload copies from such an address.
 // Weak: without them linked in, every upload goes to the copy engine.
 const void *upload_source(const void *dst, const void *src, uint64_t bytes, hipStream_t s) __attribute__((weak));
 hipError_t launch_upload(void *dst, const void *mapped_src, uint64_t bytes, hipStream_t s) __attribute__((weak));

@@ -1,5 +1,20 @@
-// Which uploads run as a kernel that reads the pinned memory itself
-// (ss_copy.hip); the copy engine takes the others.
+// Which of the pipeline's uploads run as a kernel that reads the pinned memory
+// itself (ss_copy.hip); the copy engine takes the others.
+//
+// The kernel saves the 20 to 40 us after which the engine starts behind another
+// stream's event, but it needs CUs: it waits for a workgroup of what fills the
+// GPU to end, and slows the rest.  Rounds of 96 MiB streamed in chunks of 4 to
+// 32 MiB, engine against kernel in us:
+//                       4 MiB        8 MiB       12 MiB       16 MiB       32 MiB
+//   alone           2600 2055    2500 1918    2180 1874    1950 1854    1838 1813
+//   8192^3 GEMM     3360 2816    3080 2609    2600 2501    2235 2411    1915 2104
+//     after each
+//   12 layer GEMMs  3160 2639    2820 2470    2700 2420    2275 2389    1930 2266
+//     after each
+// so it takes chunks of at most 8 MiB.  Uploads that wait for nothing gain 6 us
+// each and lose far more beside other work (8 MiB: 156 and 150 us alone, 156 and
+// 596 us beside that GEMM, 157 and 204 us beside 16 x 32768 tokens' attention),
+// so ss_upload_chunk leaves them to the engine.
 #include "ss_kernels.h"
 
 #include <cstring>
@@ -7,8 +22,7 @@
 namespace ss {
 namespace {
 
-// Larger uploads gain nothing and leave the CUs to others.
-constexpr uint64_t kMaxUpload = uint64_t(64) << 20;
+constexpr uint64_t kMaxUpload = uint64_t(8) << 20;
 
 // Non-coherent pinned memory may stay in the GPU's caches from one kernel to the
 // next, so that a kernel could read what the host has replaced since.
@@ -40,7 +54,7 @@ const void *mapped(const void *p, uint64_t bytes, hipMemoryType type, int device
 }  // namespace
 
 const void *upload_source(const void *dst, const void *src, uint64_t bytes, hipStream_t s) {
-  if (bytes > kMaxUpload) return nullptr;
+  if (bytes > kMaxUpload || bytes % 16 != 0) return nullptr;
   int current = -1;
   hipDevice_t of_stream = -1;
   if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &of_stream) != hipSuccess || of_stream != current) {
