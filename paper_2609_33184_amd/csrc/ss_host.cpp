@@ -302,6 +302,10 @@ struct Plan {
   std::vector<long> x, y;             // share and own-list ends (planning)
   size_t tail_first = 0, num_tail = 0;
   size_t units() const { return kind.size(); }
+  size_t held_bytes() const {
+    return items.capacity() * sizeof(ss::Item) + (unit_first.capacity() + wg_first.capacity()) * 4 + kind.capacity() +
+           (slots_after.capacity() + slot.capacity()) * 4 + (x.capacity() + y.capacity()) * sizeof(long);
+  }
   void reset(const ss_round *r) {
     items.clear();
     unit_first.assign(1, 0);
@@ -331,6 +335,7 @@ struct CallTokens {
   int nchunks = 0;
   std::vector<long> cum, off, start;
   std::vector<uint8_t> kind;
+  size_t held_bytes() const { return (cum.capacity() + off.capacity() + start.capacity()) * sizeof(long) + kind.capacity(); }
   void set(const ss_round *r, int n, const int32_t *len) {
     const int B = r->B;
     nchunks = n;
@@ -515,7 +520,9 @@ bool fits_one_launch(const Plan &plan) {
 // plan is rebuilt from scratch in each): a call's plan used to cost two dozen
 // allocations and a search per cut, 3.4 us for one request in 4 chunks and 37
 // us for 32 requests in 16 (now 0.9 and 19 us; CPU time of the call without its
-// launch).
+// launch).  A call that needs more than kScratchKeep (64 requests in 32 chunks
+// take a tenth of it) leaves nothing.
+constexpr size_t kScratchKeep = 768 << 10;
 struct PlanScratch {
   CallTokens tokens;
   Plan plan, tail;
@@ -524,6 +531,12 @@ PlanScratch &plan_scratch() {
   static thread_local PlanScratch s;
   return s;
 }
+struct PlanUse {   // for the length of a call
+  ~PlanUse() {
+    PlanScratch &s = plan_scratch();
+    if (s.tokens.held_bytes() + s.plan.held_bytes() + s.tail.held_bytes() > kScratchKeep) s = PlanScratch();
+  }
+};
 
 // Plan a call of `total` tokens into plan_scratch().plan.
 ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long total) {
@@ -773,6 +786,7 @@ ss_status enqueue_history(ss_round *r, int nchunks, const void *const *k, const 
 
 ss_status attend_history(ss_round *r, int nchunks, const void *const *k, const void *const *v, const int32_t *len,
                          hipEvent_t wait_before, hipEvent_t signal_after, hipStream_t stream) {
+  const PlanUse use;
   Prepared pr;
   ss_status s = prepare_history(r, nchunks, k, v, len, &pr);
   if (s != SS_OK) return s;
@@ -1096,6 +1110,7 @@ ss_status ss_pipeline_attend_chunks(ss_pipeline *p, ss_round *r, int32_t num_chu
   }
   // everything that can be refused is checked (and the launches planned)
   // before the upload is enqueued
+  const PlanUse use;
   Prepared pr;
   s = prepare_history(r, num_chunks, kk.data(), vv.data(), len, &pr);
   if (s != SS_OK) return s;
