@@ -16,6 +16,12 @@ int main() {
     scenario("1 x 32768, 4 KV heads (64 slots)", 1, 32, 4, {6}, {32768}, 4096, 0, layout, 8, 0, 0, 0, 64);
     scenario("1 x 20000, 4 KV heads (39 shares)", 1, 32, 4, {4}, {20000}, 4096, 0, layout, 8, 0, 0, 0, 39);
     scenario("1 x 16384, 4 KV heads (32 slots)", 1, 32, 4, {4}, {16384}, 4096, 0, layout, 8, 0, 0, 0, 32);
+    // never fewer workgroups than 32 slots a request allow: two per CU for row-split units, shares of 128 tokens
+    scenario("4 x 4400, 64 rows", 4, 8, 1, {8, 8, 8, 8}, {4400, 4400, 4400, 4400}, 4400, 0, layout, 1, 0, 0, 0, 69);
+    scenario("4 x 4400, 24 rows", 4, 4, 1, {6, 6, 6, 6}, {4400, 4400, 4400, 4400}, 4400, 0, layout, 1, 0, 0, 0, 69);
+    scenario("3 x 6000, 48 rows", 3, 8, 1, {6, 6, 6}, {6000, 6000, 6000}, 6000, 0, layout, 1, 0, 0, 0, 70);
+    scenario("4 x 8192, 64 rows", 4, 8, 1, {8, 8, 8, 8}, {8192, 8192, 8192, 8192}, 4096, 0, layout, 2, 0, 0, 0, 128);
+    scenario("4 x 32768, 64 rows", 4, 8, 1, {8, 8, 8, 8}, std::vector<int>(4, 32768), 8192, 0, layout, 4, 0, 0, 0, 256);
     scenario("4 x 70000, 1 KV head", 4, 8, 1, {8, 1, 3, 5}, {70000, 1, 40000, 33}, 9000, 0, layout, 8);
     scenario("1 x 400000, 1 KV head", 1, 8, 1, {8}, {400000}, 20000, 0, layout, 20);
     scenario("per-chunk calls", 1, 32, 4, {8}, {100000}, 40000, 0, layout, 1);
