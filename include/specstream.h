@@ -95,8 +95,10 @@ typedef struct {
                                (one workgroup per CU; two per CU for calls
                                with a request of more than 32 rows per KV head
                                and for calls of short shares, below 2048
-                               tokens, that span requests or have 1 or 2 rows
-                               per KV head);
+                               tokens, that span requests or are all of 1 or 2
+                               rows per KV head; rounds of at most 4 (request,
+                               KV head) pairs keep to one per CU where 32
+                               shares a request would be fewer);
                                else a multiple of 32                           */
   int32_t mfma_min_rows;    /* rows per KV head (n_b * G) from which the bf16
                                MFMA path is used; fewer (at most 4) use the

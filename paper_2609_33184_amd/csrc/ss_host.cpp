@@ -61,10 +61,11 @@ constexpr long kTargetWorkgroups = 256;
 // per CU get twice the workgroups (two fit on a CU) if many shares span
 // requests: while one of a CU's workgroups goes from unit to unit, the other
 // streams.  That is more than every second share, or in shares below kTinyShare
-// tokens every fourth.  So do calls with units of the VALU body, which keeps
-// fewer loads in flight.  A share that is one unit gains nothing from a second
-// workgroup beside it and pays twice for query staging, merge and fold.  Rounds
-// back to back, one against two per CU: 24 requests of 33 to 3000 tokens 27.7
+// tokens every fourth.  So do calls whose every unit runs the VALU body, which
+// keeps fewer loads in flight (among MFMA units it makes no difference: 8 x 4096
+// tokens, one to four of them with one row, 24.0 us with one, 24.5 with two).  A
+// share that is one unit gains nothing from a second workgroup beside it and
+// pays twice for query staging, merge and fold.  Rounds back to back, one against two per CU: 24 requests of 33 to 3000 tokens 27.7
 // and 23.2 us, 64 of 100 to 1500 39.8 and 36.4, 8 of 200 to 8000 19.9 and 19.2,
 // 8 x 8191 with one row per KV head 45.4 and 44.8; but 16 x 2000 tokens 29.5
 // and 33.5, 8 x 4096 28.0 and 29.9, 16 of 500 to 5000 27.5 and 28.6, 4 x 16384
@@ -551,13 +552,13 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long t
     // Two workgroups per CU for calls with row-split units, whose every step is
     // a barrier-bound chain of LDS and MFMA latencies (16 x 32768 tokens with
     // 64 rows: 341 us a round, 375 with one), and for the short shares above.
-    bool wide = false, valu = false;
+    bool wide = false, valu = true;
     int requests = 0;
     for (int b = 0; b < r->B; ++b) {
       if (ct.start[b + 1] == ct.start[b]) continue;
       ++requests;
       wide |= ct.kind[b] >= ss::kUnitMfma3;
-      valu |= ct.kind[b] == ss::kUnitValu;
+      valu &= ct.kind[b] == ss::kUnitValu;
     }
     W = std::max<long>(1, kTargetWorkgroups / r->Hkv);
     const long share = total / W;

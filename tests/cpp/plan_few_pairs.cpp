@@ -3,7 +3,7 @@
 // scenarios covers every token once, writes dense slots below the round's
 // count and stays inside its chunks, through both ways of starting a round.
 // Then the workgroup count of short shares: one per CU, or two where they span
-// requests or run the VALU body.
+// requests or all run the VALU body.
 #define main plan_check_main
 #include "plan_check.cpp"
 #undef main
@@ -32,6 +32,8 @@ int main() {
     scenario("17 x 2000 (over half the shares span requests)", 17, 32, 8, std::vector<int>(17, 6), std::vector<int>(17, 2000), 4096, 0, layout, 1, 0, 0, 0, 64);
     scenario("8 x 8191, one row per KV head (VALU)", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8191), 8192, 0, layout, 1, 0, 0, 0, 64);
     scenario("8 x 8192, one row per KV head", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8192), 8192, 0, layout, 1, 0, 0, 0, 32);
+    scenario("8 x 4096, one request on the VALU body", 8, 8, 8, {1, 6, 6, 6, 6, 6, 6, 6}, std::vector<int>(8, 4096), 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("8 x 4096, VALU but for a request without tokens", 8, 8, 8, {1, 1, 1, 1, 1, 1, 1, 8}, {4096, 4096, 4096, 4096, 4096, 4096, 4096, 0}, 4096, 0, layout, 1, 0, 0, 0, 64);
     scenario("4 x 4096, 64 rows", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 64);
     // A workspace allocated for a larger cohort serves a smaller one, which asks for more slots than it holds.
     auto bytes_of = [](int B, int Hq, int Hkv, int n) {
