@@ -26,8 +26,8 @@ constexpr int kClaimCounters = 64;  // words of the workspace's counter block (t
 constexpr int kUnitValu = 0;
 constexpr int kUnitMfma1 = 1;
 constexpr int kUnitMfma2 = 2;
-constexpr int kUnitMfma3 = 3;       // wide units (row-split body): only the wide kernel runs them
-constexpr int kUnitMfma4 = 4;
+constexpr int kUnitMfma3 = 3;       // wide units (row-split body, a second block of 16 rows or of 32): only the
+constexpr int kUnitMfma4 = 4;       // wide kernel runs them
 
 // Item flag: the slot has not been written in this round yet, so the kernel
 // stores its result instead of merging with (uninitialised) workspace.

@@ -627,34 +627,40 @@ __device__ __forceinline__ void mfma_unit(const P &p, const Ctx &c, unsigned cha
 
 // ---------------------------------------------------------------------------
 // Row-split MFMA body for wide query groups (33..64 rows per KV head).  The
-// four waves attend 64 tokens (two 32-token tiles) a step: wave w owns rows
-// 32 (w / 2) .. +31 and the tiles 2k + w % 2 of the unit's chain, and the two
-// waves of a row block merge their states once, at the unit's end.  Per step
-// a wave runs v_mfma_f32_32x32x16_bf16: S^T = K Q^T (8 of them, Q in
-// registers), the online softmax (a row's 32 scores lie in the two lanes l,
-// l ^ 32), O^T += V^T P^T with P as hi + lo (16).  What bounds the body is
-// the matrix, vector and LDS work that a step puts behind its barrier, and
-// the shader clock that sustained work of this kind leaves (1.6-1.7 GHz).
+// four waves attend 64 tokens (two 32-token tiles) a step: wave w owns the rows
+// from 32 (w / 2) on and the tiles 2k + w % 2 of the unit's chain, and the two
+// waves of a row block merge their states once, at the unit's end.  A block is
+// 32 rows with v_mfma_f32_32x32x16_bf16; the second block of a unit of at most
+// 48 rows is 16 rows with v_mfma_f32_16x16x32_bf16.  Per step and wave: S^T =
+// K Q^T (8 MFMAs, Q in registers), the online softmax (a row's 32 scores lie
+// in 64 / rows lanes), O^T += V^T P^T with P as hi + lo (16).  What bounds the
+// body is the matrix, vector and LDS work that a step puts behind its barrier,
+// and the shader clock that sustained work of this kind leaves (1.6-1.7 GHz).
 // Every K and V byte is read from LDS by two waves; with 16 rows per wave and
-// 32 tokens a step (v_mfma_f32_16x16x32_bf16) it was read by four, with twice
-// the barriers and row maxima per token.  Rounds back to back, that body
-// against this one: 16 x 32768 tokens with 64 rows 349 -> 339 us (LDS busy
-// 0.62 of before, VALU 0.88), 4 x 16384 with 48 rows 56.3 -> 53.7 us, 1 x
-// 32768 with 48 rows and 4 KV heads (half the CUs) 32.4 -> 27.4 us.  V's
-// second k-step is read after the first's products: 339 against 344 us with
-// both read ahead.  Two steps of loads in flight instead of one spill 23 to
-// 39 registers and take 380 us.
+// 32 tokens a step it was read by four, with twice the barriers and row maxima
+// per token.  Rounds back to back, that body, this one with 32 rows a wave
+// throughout, and this one:
+//   16 x 32768 tokens, 64 rows        350.7  337.0  337.1 us
+//   16 x 32768, 48 rows               329.8  334.4  322.0
+//   16 x 32768, 40 rows               329.5  327.8  318.3
+//   16 x 60000, 48 rows               589.8  601.3  574.2
+//   4 x 16384, 48 rows                 56.0   54.1   52.2
+// (64 rows: LDS busy 0.62 of before, VALU 0.88).  V's second k-step is read
+// after the first's products: 339 against 344 us with both read ahead.  Two
+// steps of loads in flight instead of one spill 23 to 39 registers and take 380
+// us.
 //
-// Lane l: lr = l % 32, lh = l / 32.  In the S tile lane (lr, lh) holds tokens
-// 8 (r / 4) + 4 lh + r % 4 (r = 0..15) of row lr; in O it holds
-// d = 32 db + 8 (r / 4) + 4 lh + r % 4.  The reduction index of both MFMAs is
-// permuted so that every operand is contiguous: for QK^T k-step s, lane half
-// lh covers the d-chunk 2s + lh; for PV k-step s it covers tokens
-// 16 s + {4 lh .. +3, 8 + 4 lh .. +3}, the S values the lane holds.  V is
-// read through the LDS transpose (see above): a 16-lane group reads 4 tokens
-// x 16 d.  16-byte chunk c of token row t lies at c ^ (t & 15) for K, as
-// above, and at c ^ 4 (t & 3) for V, so that the 32 lanes of a transpose read
-// (4 rows, 64 bytes each) touch every bank once.
+// Lane l of a wave of n rows: lr = l % n, lh = l / n, G = 64 / n lane groups.
+// In the S tile lane (lr, lh) holds tokens 4 G (r / 4) + 4 lh + r % 4 of row lr
+// (r = 0 .. 32 / G - 1); in O it holds d = 4 G q + 4 lh .. + 3 as piece q.  The
+// reduction index of both MFMAs is permuted so that every operand is
+// contiguous: for QK^T k-step s, lane group lh covers the d-chunk G s + lh; for
+// PV k-step s it covers tokens 16 s + {4 lh .. +3, 4 G + 4 lh .. +3}, the S
+// values the lane holds.  V is read through the LDS transpose (see above): a
+// 16-lane group reads 4 tokens x 16 d.  16-byte chunk c of token row t lies at
+// c ^ (t & 15) for K, as above, and for V at c ^ (4 (t & 3) + 2 (t / 4 & 1)), so
+// that the 32 lanes of a transpose read (4 rows, 64 bytes each, or 8 rows, 32
+// bytes each) touch every bank once.
 //
 // Step k is staged in buffer k % 2 by all waves together (wave w loads tokens
 // 16 (w / 2) .. +15 of its tile), with one workgroup barrier; each wave keeps
@@ -674,12 +680,18 @@ constexpr int kRowsMergeBytes = kWaves * (8 * 64 * 16 + 2 * 32 * 4);
 constexpr int kRowsLdsBytes = 2 * kRowsStepBytes > kRowsMergeBytes ? 2 * kRowsStepBytes : kRowsMergeBytes;
 static_assert(kRowsGroup % 2 == 0 && kRowsGroup % kRowsAhead == 0, "step i of a group uses buffer i % 2");
 
-template <typename P>
-__device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned char *smem, const UnitArg &ua, int tx, int g) {
-  const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
-  const int rb = w >> 1, th = w & 1;                       // row block, tile parity
-  const int lane = tx & 63;
-  const int lr = lane & 31, lh = lane >> 5;
+// A wave's part of a unit: rows 32 rb .. 32 rb + ROWS - 1, the tiles of parity w % 2.
+template <int ROWS, typename P>
+__device__ __forceinline__ void rows_wave(const P &p, const Ctx &cx, unsigned char *smem, const UnitArg &ua, int w, int rb,
+                                          int lane, int g) {
+  static_assert(ROWS == 32 || ROWS == 16, "v_mfma_f32_32x32x16_bf16 or v_mfma_f32_16x16x32_bf16");
+  using Acc = std::conditional_t<ROWS == 32, f32x16_t, f32x4_t>;
+  constexpr int kGroups = 64 / ROWS;                       // lane groups that share a row
+  constexpr int kQSteps = 16 / kGroups, kPSteps = 2 / (kGroups / 2);
+  constexpr int kScores = 32 / kGroups;                    // of a tile, per lane
+  constexpr int kBlocks = kHeadDim / ROWS, kPieces = 32 / kGroups;   // accumulators of ROWS d each; 16-byte pieces of them
+  const int th = w & 1;                                    // tile parity
+  const int lr = lane % ROWS, lh = lane / ROWS;            // row, lane group
   const int i0 = unit_i0(ua.word);
   const int M = unit_cand(ua) * cx.G;
   const int ntiles = (int)ua.ntiles;
@@ -690,15 +702,15 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
   const float sl2 = cx.sl2;
 
   // Q^T operand (B[k = d][j = row]) of row 32 rb + lr, k-step s: d-chunk
-  // 2s + lh.  A padding row (>= M) gets an offset past the end: zeros.
+  // kGroups s + lh.  A padding row (>= M) gets an offset past the end: zeros.
   const int row = 32 * rb + lr;
   const __amdgpu_buffer_rsrc_t qrs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t *>(cx.q), (short)0, (int)(cx.R * kRowBytes), kBufferFlags);
   const uint32_t qoff = row < M ? (uint32_t)global_row(cx, ua.q_row0, g, row) * kRowBytes + 16 * lh : 0x80000000u;
-  bf16x8_t qop[8];
+  bf16x8_t qop[kQSteps];
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    qop[s] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 32 * s, 0, 0));
+  for (int s = 0; s < kQSteps; ++s)
+    qop[s] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 16 * kGroups * s, 0, 0));
   __builtin_amdgcn_sched_barrier(0);   // the query loads go out first
 
   // loads of tile t (2k + th): K rows 16 rb + 4j + sq, then the same V rows.
@@ -735,21 +747,18 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
     for (int j = 0; j < 4; ++j) {
       const int t = 16 * rb + 4 * j + sq;
       *reinterpret_cast<u32x4_t *>(buf + t * kRowBytes + 16 * (sr ^ (t & 15))) = d[j];
-      *reinterpret_cast<u32x4_t *>(buf + kTileBytes + t * kRowBytes + 16 * (sr ^ (4 * (t & 3)))) = d[4 + j];
+      *reinterpret_cast<u32x4_t *>(buf + kTileBytes + t * kRowBytes + 16 * (sr ^ (4 * sq + 2 * (j & 1)))) = d[4 + j];
     }
   };
 
   float m_run = kNegInf, l_run = 0.f;
-  f32x16_t acc[4];
+  Acc acc[kBlocks];
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
-  // transpose read of the 16-lane group (lane >> 4): row 4 lh + j / 4 of the
-  // four, d 16 ((lane >> 4) & 1) + 4 (j % 4), j = lane % 16
-  const int vrow = 4 * lh + (sr >> 2);
-  const int vrd = vrow * kRowBytes + 16 * (2 * (sq & 1) + ((sr & 3) >> 1)) + 8 * (sr & 1);
-  const int vsw = 64 * (sr >> 2);
+  for (int db = 0; db < kBlocks; ++db) acc[db] = Acc{};
+  // transpose read of the 16-lane group sq: row 4 lh + j / 4 of the four,
+  // columns 4 (j % 4) of its 16 d, j = lane % 16
+  const int vrd = (4 * lh + (sr >> 2)) * kRowBytes + 16 * ((sr & 3) >> 1) + 8 * (sr & 1);
+  const int vsw = (64 * (sr >> 2) + 32 * (lh & 1)) ^ (ROWS == 32 ? 32 * (sq & 1) : 0);
   const int krd = lr * kRowBytes, ksw = 16 * (lh ^ (lr & 15));
   Cursor cur(ua);   // of the tile being attended
 
@@ -758,22 +767,35 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
     if (t >= cur.end) cur.seek(p, i0, t);
     const int tb = (t - cur.base) * kTile, count = cur.count;
     const unsigned char *vs = buf + kTileBytes;
-    f32x16_t c;
+    auto k_operand = [&](int s, int t0) {
+      return *reinterpret_cast<const bf16x8_t *>(buf + t0 * kRowBytes + krd + (ksw ^ (16 * kGroups * s)));
+    };
+    float c[kScores];
+    if constexpr (ROWS == 32) {
+      f32x16_t x = {};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) c[r] = 0.f;
+      for (int s = 0; s < kQSteps; ++s) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(s, 0), qop[s], x, 0, 0, 0);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const bf16x8_t kop = *reinterpret_cast<const bf16x8_t *>(buf + krd + (ksw ^ (32 * s)));
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qop[s], c, 0, 0, 0);
+      for (int r = 0; r < kScores; ++r) c[r] = x[r];
+    } else {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        f32x4_t x = {};
+#pragma unroll
+        for (int s = 0; s < kQSteps; ++s)
+          x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(s, 16 * u), qop[s], x, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[4 * u + r] = x[r];
+      }
     }
     // the V^T operands of k-step 0 go out now, so their LDS latency hides behind the softmax
-    bf16x8_t vop[4];
+    bf16x8_t vop[kBlocks];
     auto load_v = [&](int s) {
 #pragma unroll
-      for (int db = 0; db < 4; ++db) {
-        const unsigned char *a = vs + vrd + ((64 * db) ^ vsw) + 16 * s * kRowBytes;
+      for (int db = 0; db < kBlocks; ++db) {
+        const unsigned char *a = vs + vrd + ((2 * ROWS * db) ^ vsw) + 16 * s * kRowBytes;
         const s16x4_t v0 = lds_read_tr16(a);
-        const s16x4_t v1 = lds_read_tr16(a + 8 * kRowBytes);
+        const s16x4_t v1 = lds_read_tr16(a + 4 * kGroups * kRowBytes);
         vop[db] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
       }
     };
@@ -787,25 +809,25 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
     // item's last, partial tile needs the token mask.
     if (tb + kTile > count) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) c[r] = tb + 8 * (r >> 2) + 4 * lh + (r & 3) < count ? c[r] : kNegInf;
+      for (int r = 0; r < kScores; ++r) c[r] = tb + 4 * kGroups * (r >> 2) + 4 * lh + (r & 3) < count ? c[r] : kNegInf;
     }
     float mx = c[0];
 #pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, c[r]);
-    const float mn = fmaxf(m_run, x32_max(mx) * sl2);
+    for (int r = 1; r < kScores; ++r) mx = fmaxf(mx, c[r]);
+    const float mn = fmaxf(m_run, (ROWS == 32 ? x32_max(mx) : xgroup_max(mx)) * sl2);
     // Eq. 14's rescale, only when some row's maximum rose (elsewhere the
     // factor is exactly 1)
     if (__builtin_amdgcn_ballot_w64(mn > m_run)) {
       const float alpha = exp2_fast(m_run - mn);
       l_run *= alpha;
 #pragma unroll
-      for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+      for (int db = 0; db < kBlocks; ++db) acc[db] *= alpha;
       m_run = mn;
     }
-    bf16x8_t phi[2], plo[2];
+    bf16x8_t phi[kPSteps], plo[kPSteps];
     float ls = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < kScores; ++r) {
       const float pe = exp2_fast(__builtin_fmaf(c[r], sl2, -mn));
       const __bf16 h = (__bf16)pe;
       const float hf = (float)h;
@@ -818,13 +840,20 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
 
     __builtin_amdgcn_sched_barrier(0);
 
+    auto weigh = [&](const bf16x8_t &weights) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+      for (int db = 0; db < kBlocks; ++db) {
+        if constexpr (ROWS == 32)
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[db], weights, acc[db], 0, 0, 0);
+        else
+          acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[db], weights, acc[db], 0, 0, 0);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < kPSteps; ++s) {
       if (s) load_v(1);
-#pragma unroll
-      for (int db = 0; db < 4; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[db], phi[s], acc[db], 0, 0, 0);
-#pragma unroll
-      for (int db = 0; db < 4; ++db) acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop[db], plo[s], acc[db], 0, 0, 0);
+      weigh(phi[s]);
+      weigh(plo[s]);
     }
   };
 
@@ -844,11 +873,11 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
     }
   }
 
-  // Merge the two waves of a row block (Eq. 14): wave th keeps the d-blocks
-  // 2 th, 2 th + 1 and hands the others over through LDS.  A wave without
+  // Merge the two waves of a row block (Eq. 14): wave th keeps the pieces of
+  // half th of d and hands the others over through LDS.  A wave without
   // tiles has m = -inf, which scales its zeros by 0.  The slot's old m and l
   // are read before the barrier, as the block's first wave replaces them.
-  l_run = x32_sum(l_run);
+  l_run = ROWS == 32 ? x32_sum(l_run) : xgroup_sum(l_run);
   const bool stores = row < M;
   const bool merge_slot = !unit_fresh(ua);
   const size_t idx = (size_t)unit_slot(ua) * cx.R + (stores ? global_row(cx, ua.q_row0, g, row) : 0);
@@ -861,14 +890,22 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
   __syncthreads();                       // every wave is done with the tile buffers
   f32x4_t *sh = reinterpret_cast<f32x4_t *>(smem);
   float *m_sh = reinterpret_cast<float *>(smem + kWaves * 8 * 64 * 16), *l_sh = m_sh + kWaves * 32;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = 4 * (q & 3), db = q >> 2;
+  // piece q of the accumulators: d = 4 kGroups q + 4 lh .. + 3 of row lr
+  auto piece = [&](int q) {
     f32x4_t a;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) a[e] = th ? acc[db][r + e] : acc[2 + db][r + e];
-    sh[(w * 8 + q) * 64 + lane] = a;
-  }
+    for (int e = 0; e < 4; ++e) a[e] = ROWS == 32 ? acc[q >> 2][4 * (q & 3) + e] : acc[q][e];
+    return a;
+  };
+  auto half_piece = [&](int half, int q) {
+    const f32x4_t lo = piece(q), hi = piece(kPieces / 2 + q);
+    f32x4_t a;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = half ? hi[e] : lo[e];
+    return a;
+  };
+#pragma unroll
+  for (int q = 0; q < kPieces / 2; ++q) sh[(w * 8 + q) * 64 + lane] = half_piece(th ^ 1, q);
   if (lh == 0) {
     m_sh[w * 32 + lr] = m_run;
     l_sh[w * 32 + lr] = l_run;
@@ -880,13 +917,9 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
   const float f0 = exp2_fast(m_run - mn), f1 = exp2_fast(m2 - mn), fs = merge_slot ? exp2_fast(ms - mn) : 0.f;
   GlobalFloat *ap = cx.a + idx * kHeadDim + 64 * th + 4 * lh;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = 4 * (q & 3), db = q >> 2;
-    f32x4_t own;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) own[e] = th ? acc[2 + db][r + e] : acc[db][r + e];
-    f32x4_t o = f0 * own + f1 * sh[((w ^ 1) * 8 + q) * 64 + lane];
-    GlobalFloat4 *dst = (GlobalFloat4 *)(ap + 32 * db + 2 * r);
+  for (int q = 0; q < kPieces / 2; ++q) {
+    f32x4_t o = f0 * half_piece(th, q) + f1 * sh[((w ^ 1) * 8 + q) * 64 + lane];
+    GlobalFloat4 *dst = (GlobalFloat4 *)(ap + 4 * kGroups * q);
     if (merge_slot) o += fs * *dst;
     *dst = o;
   }
@@ -894,6 +927,17 @@ __device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned ch
     cx.m[idx] = mn;
     cx.l[idx] = f0 * l_run + f1 * l2 + fs * lsl;
   }
+}
+
+// Every wave runs the same barriers, whatever its rows.
+template <typename P>
+__device__ __forceinline__ void rows_unit(const P &p, const Ctx &cx, unsigned char *smem, const UnitArg &ua, int tx, int g) {
+  const int w = __builtin_amdgcn_readfirstlane(tx >> 6);   // wave-uniform
+  const int lane = tx & 63, rb = w >> 1;
+  if (rb == 1 && unit_kind(ua.word) == kUnitMfma3)
+    rows_wave<16>(p, cx, smem, ua, w, rb, lane, g);
+  else
+    rows_wave<32>(p, cx, smem, ua, w, rb, lane, g);
 }
 
 // ---------------------------------------------------------------------------
