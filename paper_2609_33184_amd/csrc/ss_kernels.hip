@@ -815,10 +815,11 @@ __device__ __forceinline__ void rows_wave(const P &p, const Ctx &cx, unsigned ch
 #pragma unroll
     for (int r = 1; r < kScores; ++r) mx = fmaxf(mx, c[r]);
     const float mn = fmaxf(m_run, (ROWS == 32 ? x32_max(mx) : xgroup_max(mx)) * sl2);
+    const float mb = mn == kNegInf ? 0.f : mn;   // scores of -inf alone so far: weights 0
     // Eq. 14's rescale, only when some row's maximum rose (elsewhere the
     // factor is exactly 1)
     if (__builtin_amdgcn_ballot_w64(mn > m_run)) {
-      const float alpha = exp2_fast(m_run - mn);
+      const float alpha = exp2_fast(m_run - mb);
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < kBlocks; ++db) acc[db] *= alpha;
@@ -828,7 +829,7 @@ __device__ __forceinline__ void rows_wave(const P &p, const Ctx &cx, unsigned ch
     float ls = 0.f;
 #pragma unroll
     for (int r = 0; r < kScores; ++r) {
-      const float pe = exp2_fast(__builtin_fmaf(c[r], sl2, -mn));
+      const float pe = exp2_fast(__builtin_fmaf(c[r], sl2, -mb));
       const __bf16 h = (__bf16)pe;
       const float hf = (float)h;
       const __bf16 lo = (__bf16)(pe - hf);
@@ -913,8 +914,8 @@ __device__ __forceinline__ void rows_wave(const P &p, const Ctx &cx, unsigned ch
   __syncthreads();
   if (!stores) return;
   const float m2 = m_sh[(w ^ 1) * 32 + lr], l2 = l_sh[(w ^ 1) * 32 + lr];
-  const float mn = fmaxf(fmaxf(m_run, m2), ms);
-  const float f0 = exp2_fast(m_run - mn), f1 = exp2_fast(m2 - mn), fs = merge_slot ? exp2_fast(ms - mn) : 0.f;
+  const float mn = fmaxf(fmaxf(m_run, m2), ms), mb = mn == kNegInf ? 0.f : mn;
+  const float f0 = exp2_fast(m_run - mb), f1 = exp2_fast(m2 - mb), fs = merge_slot ? exp2_fast(ms - mb) : 0.f;
   GlobalFloat *ap = cx.a + idx * kHeadDim + 64 * th + 4 * lh;
 #pragma unroll
   for (int q = 0; q < kPieces / 2; ++q) {

@@ -50,3 +50,41 @@ def _oracle(w):
     if key not in _CACHE:
         _CACHE[key] = oracle_full(w)
     return _CACHE[key]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group,cand", [(8, 8), (6, 8), (5, 7)])
+@pytest.mark.parametrize("masked", [(32, 64), (0, 32), (32, 96), (0, 100)])
+def test_keys_of_minus_infinity(group, cand, masked):
+    """A whole tile of scores at -inf weighs nothing, whichever wave attends it first.
+
+    Queries are positive, so a key of -inf scores -inf for every row; the
+    tokens [lo, hi) of each request have such keys.
+    """
+    lens, lo, hi = [100, 64, 131], *masked
+    w = W.custom(lens, [cand] * len(lens), num_q_heads=group, num_kv_heads=1, chunk_tokens=256, seed_base=58)
+    b = H.RoundBuffers(w)
+    b.q.abs_().clamp_(min=0.01)
+    b.out.fill_(float("nan"))
+    (k, v), = H.hbm_history(w)
+    starts = [sum(lens[:i]) for i in range(len(lens))]
+    for s0, n in zip(starts, lens):
+        k[s0 + lo:s0 + min(hi, n)] = float("-inf")
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    H.run_round(b, [(k, v)], s.cuda_stream)
+    s.synchronize()
+    for i, n in enumerate(lens):
+        r = slice(i * cand, (i + 1) * cand)
+        q = b.q[r].double().reshape(cand * group, 128)
+        keys = torch.cat([k[starts[i]:starts[i] + n, 0], b.kc[r, 0]]).double()
+        vals = torch.cat([v[starts[i]:starts[i] + n, 0], b.vc[r, 0]]).double()
+        seen = torch.cat([torch.ones(cand, n, device="cuda"), torch.ones(cand, cand, device="cuda").tril()], 1).bool()
+        # not a matrix product: 0 x inf has no part in the scores
+        x = (q[:, None, :] * keys[None]).sum(-1) * w.softmax_scale
+        x = x.masked_fill(~seen.repeat_interleave(group, 0), float("-inf"))
+        ref = torch.softmax(x, 1) @ vals
+        what = f"G={group} n={cand} request {i} masked {masked}"
+        assert_parity(b.out[r].double().reshape(cand * group, 128).cpu().numpy(), ref.cpu().numpy(), what, rel_l2=1e-5)
+        assert_parity(b.lse[r].double().reshape(-1).cpu().numpy(), torch.logsumexp(x, 1).cpu().numpy(), what + " lse",
+                      max_abs=1e-4, rel_l2=1e-5)
