@@ -248,7 +248,7 @@ ss_status ss_pipeline_create(ss_pipeline **out, void *staging0, void *staging1, 
  * len as in ss_attend_history_chunk.  The chunk may belong
  * to any round (e.g. the next layer), so transfers run ahead across layer
  * boundaries.  Uploads of at most 8 MiB, from a 16-byte-aligned address inside
- * one coherent allocation of the copy stream's GPU, are a kernel of at most 16
+ * one coherent allocation of the copy stream's GPU, are a kernel of at most 32
  * workgroups on copy_stream, which starts sooner than the copy engine; larger
  * ones are the copy engine's.  Beside work that fills the GPU for long, larger
  * chunks, transfer batches or ss_upload_chunk keep uploads off the CUs. */

@@ -16,34 +16,45 @@ namespace {
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kCopyThreads = 256;
-constexpr int kCopyDepth = 4;      // 16-byte loads in flight per thread
-// 16 workgroups keep 256 KiB in flight, which covers the link's latency; more
-// only queue up in front of it (the streamed round above: 1252 us with 16, 1280
-// with 32, 1283 with 64, 1344 with 128) and take CUs from the attention.
-constexpr unsigned kCopyWgs = 16;
+// At most 16 VGPRs a wave (8 of the attribute's units), so that a workgroup
+// finds room on a CU that two of the wide history kernel share: two 16-byte
+// loads in flight and one offset.  32 workgroups then keep 256 KiB in flight,
+// which covers the link's latency.  The same in 16 workgroups of four loads
+// (28 VGPRs) took 2900 instead of 2358 us for a round streamed in 4 MiB chunks
+// beside other history launches, and is equal alone (8 MiB chunks: 1277 us);
+// more in flight only queues up in front of the link (32 workgroups of four
+// loads 1280, 64 1283, 128 1344 us where 16 took 1252).
+constexpr int kCopyDepth = 2;
+constexpr unsigned kCopyWgs = 32;
+constexpr int kBufferFlags = 0x00020000;   // buffer resource word 3: 32-bit data format, raw offsets
+constexpr int kOnce = 2;                   // non-temporal: every byte is read once
 
-__global__ void __launch_bounds__(kCopyThreads) copy_kernel(const u32x4_t *src, u32x4_t *dst, uint64_t n) {
-  constexpr uint64_t kBlock = (uint64_t)kCopyThreads * kCopyDepth;
-  const uint64_t blocks = n / kBlock;
-  for (uint64_t b = blockIdx.x; b < blocks; b += gridDim.x) {
-    const uint64_t i = b * kBlock + threadIdx.x;
+__global__ void __launch_bounds__(kCopyThreads) __attribute__((amdgpu_num_vgpr(8))) copy_kernel(const void *src, void *dst,
+                                                                                            uint32_t bytes) {
+  constexpr uint32_t kRow = kCopyThreads * 16, kBlock = kRow * kCopyDepth;
+  const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(src), (short)0, (int)bytes, kBufferFlags);
+  const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc(dst, (short)0, (int)bytes, kBufferFlags);
+  const uint32_t blocks = bytes / kBlock, t = threadIdx.x * 16;
+  for (uint32_t b = blockIdx.x; b < blocks; b += gridDim.x) {
     u32x4_t v[kCopyDepth];
 #pragma unroll
-    for (int k = 0; k < kCopyDepth; ++k) v[k] = __builtin_nontemporal_load(src + i + k * kCopyThreads);
+    for (int k = 0; k < kCopyDepth; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(from, t, b * kBlock + k * kRow, kOnce);
 #pragma unroll
-    for (int k = 0; k < kCopyDepth; ++k) dst[i + k * kCopyThreads] = v[k];
+    for (int k = 0; k < kCopyDepth; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], to, t, b * kBlock + k * kRow, 0);
   }
+  // the rest: words past the end read zero and are not written
   if (blockIdx.x == gridDim.x - 1)
-    for (uint64_t i = blocks * kBlock + threadIdx.x; i < n; i += kCopyThreads) dst[i] = src[i];
+    for (uint32_t o = blocks * kBlock; o < bytes; o += kRow)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(from, o + t, 0, kOnce), to, o + t, 0, 0);
 }
 
 }  // namespace
 
 hipError_t launch_upload(void *dst, const void *mapped_src, uint64_t bytes, hipStream_t s) {
-  const uint64_t n = bytes / 16, blocks = n / (kCopyThreads * kCopyDepth);
+  if (bytes == 0 || bytes % 16 != 0 || bytes >= (uint64_t(1) << 31)) return hipErrorInvalidValue;
+  const uint64_t blocks = bytes / (kCopyThreads * 16 * kCopyDepth);
   const unsigned grid = (unsigned)(blocks < 1 ? 1 : blocks > kCopyWgs ? kCopyWgs : blocks);
-  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyThreads), 0, s, static_cast<const u32x4_t *>(mapped_src),
-                     static_cast<u32x4_t *>(dst), n);
+  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyThreads), 0, s, mapped_src, dst, (uint32_t)bytes);
   return hipGetLastError();
 }
 

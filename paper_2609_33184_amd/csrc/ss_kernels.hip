@@ -1146,7 +1146,7 @@ static_assert(kRowsLdsBytes <= kChunkLdsBytes && 2 * kChunkLdsBytes <= 160 * 102
 // the loop instead of indexing outside the tail.
 // ---------------------------------------------------------------------------
 template <bool Wide, typename P>
-__global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
+__device__ __forceinline__ void attend_units(const P &p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kChunkLdsBytes];
   __shared__ uint32_t claim_sh;
   // Grid (Hkv, workgroups, 1) or (1, workgroups, Hkv): see the launch.
@@ -1223,6 +1223,23 @@ __global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
         valu_unit<kMaxValuRows>(p, cx, lds, ua, tx, g);
     }
   }
+}
+
+template <typename P>
+__global__ void __launch_bounds__(256, 2) chunk_attn(const P p) {
+  attend_units<false>(p);
+}
+// The wide kernel, of which two workgroups share a CU for the whole of a launch,
+// keeps to 248 VGPRs (124 of the attribute's units): the 16 left of a SIMD's 512
+// are what a wave of the upload kernel needs.  With 251, a round streamed in 8
+// MiB chunks beside rounds of 16 x 32768 tokens and 64 rows took 4774 us, as
+// every upload waited for a launch to end; with 248 it takes 2575 us (2514 us
+// with the copy engine) and the launches the same time.  The narrow kernel
+// leaves half of a CU free as a rule, and at 248 takes 380 us instead of 377 for
+// 16 x 32768 tokens by chunk.
+template <typename P>
+__global__ void __launch_bounds__(256, 2) __attribute__((amdgpu_num_vgpr(124))) chunk_attn_wide(const P p) {
+  attend_units<true>(p);
 }
 
 __global__ void __launch_bounds__(64) clear_counters_kernel(uint32_t *c, int n) {
@@ -1521,7 +1538,10 @@ hipError_t launch_chunk_as(const ChunkParams &p, int wgs, hipStream_t s) {
   }
   // the heads are the fast grid dimension, or the workgroups are
   const dim3 grid = p.heads_fast ? dim3(p.Hkv, wgs, 1) : dim3(1, wgs, p.Hkv);
-  hipLaunchKernelGGL((chunk_attn<Wide, D>), grid, dim3(256), 0, s, d);
+  if constexpr (Wide)
+    hipLaunchKernelGGL(chunk_attn_wide<D>, grid, dim3(256), 0, s, d);
+  else
+    hipLaunchKernelGGL(chunk_attn<D>, grid, dim3(256), 0, s, d);
   return hipGetLastError();
 }
 

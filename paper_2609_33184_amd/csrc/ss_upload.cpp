@@ -11,6 +11,12 @@
 //     after each
 //   12 layer GEMMs  3160 2639    2820 2470    2700 2420    2275 2389    1930 2266
 //     after each
+//   that GEMM all   8493 8384    7459 7541
+//     the time
+//   16 x 32768      2645 2261    2506 2085
+//     tokens too
+//   the same with   4672 4616    2637 2624
+//     64 rows
 // so it takes chunks of at most 8 MiB.  Uploads that wait for nothing gain 6 us
 // each and lose far more beside other work (8 MiB: 156 and 150 us alone, 156 and
 // 596 us beside that GEMM, 157 and 204 us beside 16 x 32768 tokens' attention),
