@@ -247,7 +247,7 @@ ss_status ss_pipeline_create(ss_pipeline **out, void *staging0, void *staging1, 
  * (SS_KV_HEAD_MAJOR_KV: the chunk's one [Hkv][sum_b len_b][2][d] buffer);
  * len as in ss_attend_history_chunk.  The chunk may belong
  * to any round (e.g. the next layer), so transfers run ahead across layer
- * boundaries.  Uploads of at most 8 MiB, from a 16-byte-aligned address inside
+ * boundaries.  Uploads of at most 16 MiB, from a 16-byte-aligned address inside
  * one coherent allocation of the copy stream's GPU, are a kernel of at most 32
  * workgroups on copy_stream, which starts sooner than the copy engine; larger
  * ones are the copy engine's.  Beside work that fills the GPU for long, larger

@@ -1,26 +1,23 @@
 // Which of the pipeline's uploads run as a kernel that reads the pinned memory
 // itself (ss_copy.hip); the copy engine takes the others.
 //
-// The kernel saves the 20 to 40 us after which the engine starts behind another
-// stream's event, but it needs CUs: it waits for a workgroup of what fills the
-// GPU to end, and slows the rest.  Rounds of 96 MiB streamed in chunks of 4 to
-// 32 MiB, engine against kernel in us:
-//                       4 MiB        8 MiB       12 MiB       16 MiB       32 MiB
-//   alone           2600 2055    2500 1918    2180 1874    1950 1854    1838 1813
-//   8192^3 GEMM     3360 2816    3080 2609    2600 2501    2235 2411    1915 2104
-//     after each
-//   12 layer GEMMs  3160 2639    2820 2470    2700 2420    2275 2389    1930 2266
-//     after each
-//   that GEMM all   8493 8384    7459 7541
-//     the time
-//   16 x 32768      2645 2261    2506 2085
-//     tokens too
-//   the same with   4672 4616    2637 2624
-//     64 rows
-// so it takes chunks of at most 8 MiB.  Uploads that wait for nothing gain 6 us
-// each and lose far more beside other work (8 MiB: 156 and 150 us alone, 156 and
-// 596 us beside that GEMM, 157 and 204 us beside 16 x 32768 tokens' attention),
-// so ss_upload_chunk leaves them to the engine.
+// The kernel saves what the engine loses behind another stream's event, 20 us
+// and more a chunk.  But it needs CUs, it waits for a workgroup of what fills
+// the GPU to end, and what shares a CU with it waits behind its reads over the
+// link (a 48 us GEMM ends with the upload beside it).  Rounds of 80 to 96 MiB,
+// one request streamed in chunks of the sizes below, engine and kernel in us:
+//                          8 MiB      16 MiB     20 MiB     24 MiB     32 MiB
+//   alone                2810 1915  2250 1918  1620 1526  1870 1825  1838 1810
+//   a GEMM after each    2940 2590  3000 2735  1715 1990  1966 2220  1889 2064
+//   12 layer GEMMs each  2730 2460  3100 2518  1910 2018  2150 2300  1961 2242
+//   beside that GEMM     7459 7541
+//   beside attention     2506 2085
+//     of 64 rows         2637 2624
+// (GEMMs 8192^3 and 256 x 4096 x 14336; attention of 16 x 32768 tokens), so it
+// takes chunks of at most 16 MiB.  Uploads that wait for nothing gain 6 us each
+// and lose far more beside other work (8 MiB: 156 and 150 us alone, 156 and 596
+// us beside the GEMM, 157 and 204 us beside the attention), so ss_upload_chunk
+// leaves them to the engine.
 #include "ss_kernels.h"
 
 #include <cstring>
@@ -28,7 +25,7 @@
 namespace ss {
 namespace {
 
-constexpr uint64_t kMaxUpload = uint64_t(8) << 20;
+constexpr uint64_t kMaxUpload = uint64_t(16) << 20;
 
 // Non-coherent pinned memory may stay in the GPU's caches from one kernel to the
 // next, so that a kernel could read what the host has replaced since.

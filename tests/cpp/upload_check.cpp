@@ -144,9 +144,9 @@ int main() {
   stream_device = 1;
   expect("copy stream of another GPU", 'e', way(D1, H1, MT));
   stream_device = 0;
-  // past 8 MiB, and outside the pipeline, uploads keep off the CUs
-  expect("8 MiB", 'k', way(D1, H1, 8 * MT));
-  expect("8 MiB and a token", 'e', way(D1, H1, 8 * MT + 1));
+  // past 16 MiB, and outside the pipeline, uploads keep off the CUs
+  expect("16 MiB", 'k', way(D1, H1, 16 * MT));
+  expect("16 MiB and a token", 'e', way(D1, H1, 16 * MT + 1));
   for (size_t bytes : {(size_t)16, (size_t)4096, 8 * M}) {
     ups.clear();
     CHECK(ss_upload_chunk((void *)D1, (void *)H1, bytes, nullptr, nullptr, nullptr) == SS_OK, "%s", ss_last_error());

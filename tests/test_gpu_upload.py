@@ -93,7 +93,7 @@ class _Pipe:
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("off", [0, 16, 4])
-@pytest.mark.parametrize("tokens", [1, 31, 32, 33, 65, 16 * 32, 17 * 32 + 1, (8 << 20) // TOKEN, (8 << 20) // TOKEN + 1])
+@pytest.mark.parametrize("tokens", [1, 31, 32, 33, 65, 16 * 32, 17 * 32 + 1, (16 << 20) // TOKEN, (16 << 20) // TOKEN + 1])
 def test_pipeline_upload_bytes(tokens, off):
     ss.load()
     n = tokens * TOKEN
