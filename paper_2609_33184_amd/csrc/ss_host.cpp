@@ -821,7 +821,8 @@ bool check_out(float *out, float *lse, ss_status *s) {
   return true;
 }
 
-// The finalize kernel: one wave per query row.
+// The finalize kernel: half a wave per query row, or in small rounds a
+// workgroup's four waves per pair of rows.
 ss_status enqueue_finalize(ss_round *r, float *out, float *lse, hipStream_t stream) {
   static thread_local ss::FinalParams p;
   p.kc = r->kc;

@@ -98,7 +98,8 @@ struct ChunkHeader {
 
 // Unit record.  word packs the unit's first item i0 (within the launch), its
 // item count nit (1..kMaxChain; 0 = no unit), the body kind and the chunk of
-// item i0; ntiles is the chain's tile count.
+// item i0; ntiles is the chain's tile count.  The kernels take n_cand from the
+// item; here it fills the record to 16 bytes.
 struct UnitRec {
   uint32_t word;
   uint32_t ntiles;

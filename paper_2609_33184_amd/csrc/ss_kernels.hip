@@ -113,8 +113,8 @@ __device__ __forceinline__ float xgroup_sum(float x) { return x32_sum(x16_sum(x)
 // K/V load went out 0.4 us later.  k, v point at the first item's first token
 // of KV head 0.  Rounds back to back, before and after: 1 x 16384 tokens 19.4 ->
 // 18.3 us, 24 ragged short requests 26.6 -> 25.5 us, 16 x 32768 tokens by chunk
-// (8 launches) 386.5 -> 382.9 us, in one call 308.6 -> 307.5 us, 32 x 131072
-// tokens 2395 -> 2391 us (with tables of 42 KB for the last, 2399 us).
+// (8 launches) 386.5 -> 382.9 us; rounds of one long launch do not change (16 x
+// 32768 in one call 308, 32 x 131072 2393 us).
 struct UnitArg {
   const uint16_t *k, *v;
   uint64_t hs;           // elements between KV heads
@@ -1490,10 +1490,14 @@ using ChunkLarge = ChunkArgs<kMaxUnits, kMaxItems, kMaxWgs, false>;   // 54 KB
 // second unit than attending it (the units of 24 requests of 33 to 3000 tokens
 // ended within 13 us of the launch's start, those that came second at 22).
 // Such a launch, of at most kSpreadTiles tiles per share, gives every unit a
-// workgroup, if they nearly all run at once (two per CU).  Rounds back to back,
-// without and with: those 24 requests in one call (7 tiles a share, 688
-// workgroups) 25.6 -> 23.7 us, by chunk 47.4 -> 36.5 us.  Longer shares are
-// balanced as they are, and their units are not: 12 requests of 100 to 20000
+// workgroup, up to kSpreadWgs of them: 512 run at once (two per CU), the others
+// start as those end.  Rounds back to back, without and with: those 24 requests
+// in one call (7 tiles a share, 688 workgroups) 25.6 -> 23.7 us, by chunk 47.4
+// -> 36.5 us.  With 32q/8kv and requests of 33 to 1500 tokens, at a limit of 0,
+// 512, 640 and 768: 16 requests 17.7, 15.2, 15.2, 15.4 us, 28 requests 21.1,
+// 21.4, 21.5, 18.9, 32 requests 27.4, 27.5, 27.5, 21.3; no cohort of 12 to 128
+// requests with 2, 4 or 8 KV heads was slower at 768 than below.  Longer shares
+// are balanced as they are, and their units are not: 12 requests of 100 to 20000
 // tokens 24.1 us as shares, 26.5 us as units, 16 of 1000 to 16000 53.3 and 62.7.
 constexpr long kSpreadTiles = 8;
 constexpr long kSpreadWgs = 768;
@@ -1616,9 +1620,13 @@ constexpr long kSplitWgs = 1024;
 
 template <typename D>
 hipError_t launch_finalize_cand(const D &d, int n, int slots, hipStream_t s) {
-  // more slots than a half wave has lanes (rounds of few rows) are always split
-  if (slots > 64) return launch_finalize_as<kNumSlots, 4, false>(d, n, s);
-  if (slots > kBaseSlots) return launch_finalize_as<64, 4, false>(d, n, s);
+  // more slots than a half wave has lanes are always split; they come with at
+  // most 4 requests, so at most 32 candidates, and never with the large table
+  if constexpr (D::kCand <= FinalSmall::kCand) {
+    if (slots > 64) return launch_finalize_as<kNumSlots, 4, false>(d, n, s);
+    if (slots > kBaseSlots) return launch_finalize_as<64, 4, false>(d, n, s);
+  }
+  if (slots > kBaseSlots) return hipErrorInvalidValue;
   if ((uint64_t)kBaseSlots * (uint32_t)d.st.R * (kHeadDim * 4) >= (uint64_t(1) << 32))
     return launch_finalize_as<kBaseSlots, 1, true>(d, n, s);
   if constexpr (D::kCand <= FinalSmall::kCand)
