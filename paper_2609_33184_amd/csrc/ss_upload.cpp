@@ -28,8 +28,13 @@ namespace {
 constexpr uint64_t kMaxUpload = uint64_t(16) << 20;
 
 // Non-coherent pinned memory may stay in the GPU's caches from one kernel to the
-// next, so that a kernel could read what the host has replaced since.
+// next, so that a kernel could read what the host has replaced since.  Default
+// memory (no flag; torch's pinned tensors) is coherent, and so is what these
+// flags ask for; with others (portable, write-combined, NUMA policy) that is
+// HIP_HOST_COHERENT's matter, which the allocation's flags don't show.
+constexpr unsigned kCoherent = hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocUncached;
 constexpr unsigned kNonCoherent = hipHostMallocNonCoherent | hipExtHostRegisterCoarseGrained;
+bool coherent(unsigned flags) { return flags == 0 || ((flags & kCoherent) != 0 && (flags & kNonCoherent) == 0); }
 
 // The address at which GPU `device` sees [p, p + bytes), if the range lies
 // inside one allocation of the wanted type there and is 16-byte aligned; else
@@ -49,7 +54,7 @@ const void *mapped(const void *p, uint64_t bytes, hipMemoryType type, int device
     return nullptr;
   }
   const uintptr_t d = reinterpret_cast<uintptr_t>(attr.devicePointer), s = reinterpret_cast<uintptr_t>(start);
-  if (type == hipMemoryTypeHost && (attr.allocationFlags & kNonCoherent) != 0) return nullptr;
+  if (type == hipMemoryTypeHost && !coherent(attr.allocationFlags)) return nullptr;
   const bool whole = d != 0 && d >= s && d - s <= size && bytes <= size - (d - s);
   return whole && attr.type == type && attr.device == device && d % 16 == 0 ? attr.devicePointer : nullptr;
 }

@@ -25,6 +25,10 @@ const Alloc allocs[] = {
     {H1 + 256 * M, 8 * M, hipMemoryTypeHost, 1, 0},            // pinned for the other GPU
     {H1 + 512 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocNonCoherent},
     {H1 + 768 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocCoherent},
+    {H1 + 1024 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocPortable},
+    {H1 + 1280 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocWriteCombined},
+    {H1 + 1536 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocMapped | hipHostMallocPortable},
+    {H1 + 1792 * M, 8 * M, hipMemoryTypeHost, 0, hipHostMallocMapped | hipHostMallocNonCoherent},
     {D0, 8 * M, hipMemoryTypeDevice, 0, 0},
     {D0 + 8 * M, 8 * M, hipMemoryTypeDevice, 0, 0},
     {D0 + 18 * M, 8 * M, hipMemoryTypeDevice, 0, 0},
@@ -138,6 +142,11 @@ int main() {
   // memory that the GPU may cache is the copy engine's: a kernel could read what an earlier one left in the cache
   expect("non-coherent source", 'e', way(D1, H1 + 512 * M, MT));
   expect("explicitly coherent source", 'k', way(D1, H1 + 768 * M, MT));
+  // without a word on coherence these follow HIP_HOST_COHERENT
+  expect("portable source", 'e', way(D1, H1 + 1024 * M, MT));
+  expect("write-combined source", 'e', way(D1, H1 + 1280 * M, MT));
+  expect("mapped source", 'k', way(D1, H1 + 1536 * M, MT));
+  expect("mapped, non-coherent source", 'e', way(D1, H1 + 1792 * M, MT));
   expect("source 8 bytes off", 'e', way(D1, H1 + 8, MT));
   expect("pinned for another GPU", 'e', way(D1, H1 + 256 * M, MT));
   expect("slot on another GPU", 'e', way(D1 + 256 * M, H1, MT));
