@@ -65,12 +65,12 @@ constexpr long kTargetWorkgroups = 256;
 // keeps fewer loads in flight (among MFMA units it makes no difference: 8 x 4096
 // tokens, one to four of them with one row, 24.0 us with one, 24.5 with two).  A
 // share that is one unit gains nothing from a second workgroup beside it and
-// pays twice for query staging, merge and fold.  Rounds back to back, one against two per CU: 24 requests of 33 to 3000 tokens 27.7
-// and 23.2 us, 64 of 100 to 1500 39.8 and 36.4, 8 of 200 to 8000 19.9 and 19.2,
-// 8 x 8191 with one row per KV head 45.4 and 44.8; but 16 x 2000 tokens 29.5
-// and 33.5, 8 x 4096 28.0 and 29.9, 16 of 500 to 5000 27.5 and 28.6, 4 x 16384
-// with 4 KV heads 28.3 and 33.6, 1 x 8192 13.4 and 14.0.  Shares keep kMinPiece
-// tokens (one tile per wave).
+// pays twice for query staging, merge and fold.  Rounds back to back, one against
+// two per CU: 24 requests of 33 to 3000 tokens 27.7 and 23.2 us, 64 of 100 to
+// 1500 39.8 and 36.4, 8 of 200 to 8000 19.9 and 19.2, 8 x 8191 with one row per
+// KV head 45.4 and 44.8; but 16 x 2000 tokens 29.5 and 33.5, 8 x 4096 28.0 and
+// 29.9, 16 of 500 to 5000 27.5 and 28.6, 4 x 16384 with 4 KV heads 28.3 and 33.6,
+// 1 x 8192 13.4 and 14.0.  Shares keep kMinPiece tokens (one tile per wave).
 constexpr long kSmallShare = 2048;
 constexpr long kTinyShare = 512;
 constexpr int kMinPiece = 128;

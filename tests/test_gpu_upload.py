@@ -17,8 +17,8 @@ import torch
 
 from paper_2609_33184_amd import specstream as ss
 
-KERNEL_BLOCK = 256 * 4 * 16
-LIMIT = 64 << 20
+BLOCK = 256 * 4 * 16
+LARGE = 64 << 20
 
 
 def _bytes(n, seed):
@@ -28,11 +28,11 @@ def _bytes(n, seed):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("src_off,dst_off", [(0, 0), (16, 48), (1, 0), (0, 8), (7, 7)])
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, KERNEL_BLOCK - 1, KERNEL_BLOCK, KERNEL_BLOCK + 16,
-                               17 * KERNEL_BLOCK + 33, LIMIT, LIMIT + 1])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, BLOCK - 1, BLOCK, BLOCK + 16,
+                               17 * BLOCK + 33, LARGE, LARGE + 1])
 def test_upload_bytes(n, src_off, dst_off):
     ss.load()
-    if n >= LIMIT and src_off not in (0, 1):
+    if n >= LARGE and src_off not in (0, 1):
         pytest.skip("large sizes: one aligned and one unaligned start")
     src = _bytes(n + src_off, n % 1000 + src_off)
     dst = torch.full((n + dst_off + 64,), 0xA5, dtype=torch.uint8, device="cuda")
@@ -48,7 +48,7 @@ def test_upload_bytes(n, src_off, dst_off):
 @pytest.mark.gpu
 def test_upload_in_a_graph():
     ss.load()
-    n = 5 * KERNEL_BLOCK + 40
+    n = 5 * BLOCK + 40
     src, dst = _bytes(n, 3), torch.zeros(n, dtype=torch.uint8, device="cuda")
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
