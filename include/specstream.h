@@ -156,8 +156,8 @@ typedef struct {
  * whole 256 bytes of the workspace given to ss_round_init).  A round of so few
  * pairs also runs, somewhat slower, on a workspace of 64 or 32 slots, so the
  * workspace of a larger cohort serves every smaller one of the same heads; one
- * that is less than a slot's states short of the bytes returned here is
- * refused.  0 if the descriptor is invalid (see ss_last_error). */
+ * that lacks 256 bytes or less of the bytes returned here is refused as a
+ * miscount.  0 if the descriptor is invalid (see ss_last_error). */
 size_t ss_round_workspace_bytes(const ss_round_desc *desc);
 
 /* Start a round (paper Sec. 4.2: state (m, l, a) = (-inf, 0, 0) per query and

@@ -185,13 +185,13 @@ struct WorkspaceLayout {
 // of that in a smaller workspace, but never below the base slots.  A loop that
 // allocates for its largest cohort can so run its smaller ones, which may ask
 // for more (16q/2kv with 8 candidates: 3 requests 6.4 MB, 2 requests 8.5 MB).
-// Less than one slot short of the whole is a miscount and stays refused: cohorts
-// of the same heads differ by at least 32 Hq rows of states, and a slot of a
-// round of few pairs has at most 32 candidates, so at most that many.
+// At most a counter block short of the whole is a miscount (the block left out,
+// or a byte) and stays refused; no cohort of the same heads asks for such a size,
+// since theirs differ by at least the states of 32 Hq rows.
 long workspace_slots(long R, long B, long Hkv, size_t bytes) {
   long slots = num_slots(B, Hkv);
   const size_t whole = WorkspaceLayout(R, slots).bytes;
-  if (bytes < whole && whole - bytes < (size_t)R * ss::kHeadDim * sizeof(float)) return slots;
+  if (bytes < whole && whole - bytes <= WorkspaceLayout::kCounterBytes) return slots;
   while (slots > ss::kBaseSlots && WorkspaceLayout(R, slots).bytes > bytes) slots /= 2;
   return slots;
 }

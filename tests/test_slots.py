@@ -84,7 +84,8 @@ def test_workspace_of_a_larger_cohort():
     for n in (3, 2, 1):
         ss.ss_round_destroy(ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, held))
         base = 32 * 128 * n * 520 + 256          # 32 slots: the least that a round takes
-        ss.ss_round_destroy(ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, base))
+        for enough in (base, max(base, need(n) - 257), max(base, need(n) - 20000)):
+            ss.ss_round_destroy(ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, enough))
         for short in (base - 1, need(n) - 1, need(n) - 256):
             with pytest.raises(ss.SpecStreamError) as e:
                 ss.ss_round_init(ss.make_desc([8] * n, *heads), 0x7f0000000000, 0x7f1000000000, short)
