@@ -10,6 +10,8 @@
 
 #include "ss_kernels.h"
 
+#include <algorithm>
+
 namespace ss {
 namespace {
 
@@ -18,14 +20,21 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kCopyThreads = 256;
 // At most 16 VGPRs a wave (8 of the attribute's units), so that a workgroup
 // finds room on a CU that two of the wide history kernel share: two 16-byte
-// loads in flight and one offset.  32 workgroups then keep 256 KiB in flight,
-// which covers the link's latency.  The same in 16 workgroups of four loads
-// (28 VGPRs) took 2900 instead of 2358 us for a round streamed in 4 MiB chunks
-// beside other history launches, and is equal alone (8 MiB chunks: 1277 us);
-// more in flight only queues up in front of the link (32 workgroups of four
-// loads 1280, 64 1283, 128 1344 us where 16 took 1252).
+// loads in flight and one offset.  16 workgroups, 128 KiB in flight, cover the
+// link's latency on an idle GPU (8 MiB chunks: 1275 us with 16 and with 32, 1291
+// with 12, 1490 with 8; more than 256 KiB only queues up in front of the link: 32
+// workgroups of four loads 1280, 64 1283, 128 1344 us where 16 took 1252).  32
+// hold their own beside other streams' work (a round streamed in 8 MiB chunks
+// beside attention 1330 us with 32, 1580 with 16), but what shares a CU with them
+// waits longer: many short requests on 1 to 2 MiB of history, whose attention
+// takes no longer than the next round's upload, get 16 (51 requests of 1 to 41
+// tokens 101 us a round with 32, 84 with 16 and 88 by the copy engine; 32
+// requests of 8 tokens 89, 80 and 89; from 4 MiB on 16 and 32 are equal there).
+// Between the two, a workgroup per 128 KiB.
 constexpr int kCopyDepth = 2;
 constexpr unsigned kCopyWgs = 32;
+constexpr unsigned kFewCopyWgs = 16;
+constexpr unsigned kCopyShare = 128 << 10;
 constexpr int kBufferFlags = 0x00020000;   // buffer resource word 3: 32-bit data format, raw offsets
 constexpr int kOnce = 2;                   // non-temporal: every byte is read once
 
@@ -53,7 +62,8 @@ __global__ void __launch_bounds__(kCopyThreads) __attribute__((amdgpu_num_vgpr(8
 hipError_t launch_upload(void *dst, const void *mapped_src, uint64_t bytes, hipStream_t s) {
   if (bytes == 0 || bytes % 16 != 0 || bytes >= (uint64_t(1) << 31)) return hipErrorInvalidValue;
   const uint64_t blocks = bytes / (kCopyThreads * 16 * kCopyDepth);
-  const unsigned grid = (unsigned)(blocks < 1 ? 1 : blocks > kCopyWgs ? kCopyWgs : blocks);
+  const uint64_t wgs = std::min<uint64_t>(kCopyWgs, std::max<uint64_t>(kFewCopyWgs, bytes / kCopyShare));
+  const unsigned grid = (unsigned)std::max<uint64_t>(1, std::min(wgs, blocks));
   hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kCopyThreads), 0, s, mapped_src, dst, (uint32_t)bytes);
   return hipGetLastError();
 }

@@ -14,7 +14,12 @@
 //   beside attention     2506 2085
 //     of 64 rows         2637 2624
 // (GEMMs 8192^3 and 256 x 4096 x 14336; attention of 16 x 32768 tokens), so it
-// takes chunks of at most 16 MiB.  Uploads that wait for nothing gain 6 us each
+// takes chunks of at most 16 MiB.  A copy stream that shares one of the four
+// hardware queues with a stream full of attention launches is the exception:
+// engine and kernel 2490 and 2983 us there (8 MiB chunks, the attention of 4 x
+// 32768 tokens), 1605 and 1326 on a queue of its own, 1776 and 1529 on that of
+// the round's stream; with 2 MiB chunks 990 and 1272, 540 and 533, 744 and 737.
+// Uploads that wait for nothing gain 6 us each
 // and lose far more beside other work (8 MiB: 156 and 150 us alone, 156 and 596
 // us beside the GEMM, 157 and 204 us beside the attention), so ss_upload_chunk
 // leaves them to the engine.

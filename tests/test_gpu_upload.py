@@ -93,7 +93,9 @@ class _Pipe:
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("off", [0, 16, 4])
-@pytest.mark.parametrize("tokens", [1, 31, 32, 33, 65, 16 * 32, 17 * 32 + 1, (16 << 20) // TOKEN, (16 << 20) // TOKEN + 1])
+@pytest.mark.parametrize("tokens", [1, 31, 32, 33, 65, 16 * 16 + 1, 16 * 32, 17 * 32 + 1, (2 << 20) // TOKEN - 1,
+                                    (2 << 20) // TOKEN + 257, (4 << 20) // TOKEN + 15, (16 << 20) // TOKEN,
+                                    (16 << 20) // TOKEN + 1])
 def test_pipeline_upload_bytes(tokens, off):
     ss.load()
     n = tokens * TOKEN
