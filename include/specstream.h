@@ -94,7 +94,7 @@ typedef struct {
                                one per workgroup and KV head; 0 = automatic
                                (one workgroup per CU; two per CU for calls
                                with a request of more than 32 rows per KV head
-                               and for calls of short shares, below 2048
+                               and for most calls of short shares, below 2048
                                tokens, that span requests or are all of 1 or 2
                                rows per KV head; rounds of at most 4 (request,
                                KV head) pairs keep to one per CU where 32

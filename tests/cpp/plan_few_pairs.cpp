@@ -3,7 +3,8 @@
 // scenarios covers every token once, writes dense slots below the round's
 // count and stays inside its chunks, through both ways of starting a round.
 // Then the workgroup count of short shares: one per CU, or two where they span
-// requests or all run the VALU body.
+// requests or all run the VALU body, and one of 128 tokens for each share of six
+// to eight tiles where one spans requests.
 #define main plan_check_main
 #include "plan_check.cpp"
 #undef main
@@ -34,6 +35,13 @@ int main() {
     scenario("8 x 8192, one row per KV head", 8, 8, 8, std::vector<int>(8, 1), std::vector<int>(8, 8192), 8192, 0, layout, 1, 0, 0, 0, 32);
     scenario("8 x 4096, one request on the VALU body", 8, 8, 8, {1, 6, 6, 6, 6, 6, 6, 6}, std::vector<int>(8, 4096), 4096, 0, layout, 1, 0, 0, 0, 32);
     scenario("8 x 4096, VALU but for a request without tokens", 8, 8, 8, {1, 1, 1, 1, 1, 1, 1, 8}, {4096, 4096, 4096, 4096, 4096, 4096, 4096, 0}, 4096, 0, layout, 1, 0, 0, 0, 64);
+    scenario("3 x 2048 (192 tokens a share, some span requests)", 3, 32, 8, std::vector<int>(3, 6), std::vector<int>(3, 2048), 2048, 0, layout, 1, 0, 0, 0, 48);
+    scenario("3 x 2037 (190 tokens a share)", 3, 32, 8, std::vector<int>(3, 6), std::vector<int>(3, 2037), 2048, 0, layout, 1, 0, 0, 0, 32);
+    scenario("7 x 1165 (254 tokens a share, some span requests)", 7, 32, 8, std::vector<int>(7, 6), std::vector<int>(7, 1165), 2048, 0, layout, 1, 0, 0, 0, 63);
+    scenario("3 x 2731 (256 tokens a share)", 3, 32, 8, std::vector<int>(3, 6), std::vector<int>(3, 2731), 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("4 x 1536 (192 tokens a share, none spans requests)", 4, 32, 8, std::vector<int>(4, 6), std::vector<int>(4, 1536), 2048, 0, layout, 1, 0, 0, 0, 32);
+    scenario("2 x 3100, one without tokens between (none spans)", 3, 32, 8, std::vector<int>(3, 6), {3100, 0, 3100}, 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("2000 and 5000 tokens (one share spans requests)", 2, 32, 8, {6, 6}, {2000, 5000}, 8192, 0, layout, 1, 0, 0, 0, 28);
     scenario("4 x 4096, 64 rows", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 64);
     // A workspace allocated for a larger cohort serves a smaller one, which asks for more slots than it holds.
     auto bytes_of = [](int B, int Hq, int Hkv, int n) {
