@@ -93,10 +93,10 @@ typedef struct {
                                split into equal shares of about this many,
                                one per workgroup and KV head; 0 = automatic
                                (one workgroup per CU; two per CU for calls
-                               with a request of more than 32 rows per KV head
-                               and for most calls of short shares, below 2048
-                               tokens, that span requests or are all of 1 or 2
-                               rows per KV head; rounds of at most 4 (request,
+                               of long shares, from 2048 tokens on, with a
+                               request of more than 32 rows per KV head, and
+                               for most calls of shorter shares that span
+                               requests or are all of 1 or 2 rows per KV head; rounds of at most 4 (request,
                                KV head) pairs keep to one per CU where 32
                                shares a request would be fewer);
                                else a multiple of 32                           */

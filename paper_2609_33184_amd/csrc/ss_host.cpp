@@ -572,9 +572,16 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long t
   if (r->split_tokens > 0) {
     W = (total + r->split_tokens - 1) / r->split_tokens;
   } else {
-    // Two workgroups per CU for calls with row-split units, whose every step is
-    // a barrier-bound chain of LDS and MFMA latencies (16 x 32768 tokens with
-    // 64 rows: 341 us a round, 375 with one), and for the short shares above.
+    // Two workgroups per CU for long shares with row-split units, whose every
+    // step is a barrier-bound chain of LDS and MFMA latencies (16 x 32768 tokens
+    // with 64 rows: 341 us a round, 375 with one), and for the short shares above.
+    // Short shares of row-split units are bound by what a unit costs at its start
+    // and end, so one per CU is better there, and two leave no place for the units
+    // of shares that span requests: rounds of four calls with 48 rows, two and one
+    // per CU, 4 x 2250 tokens 65.2 and 50.8 us, 9 of 400 to 2400 92 and 76, 4 x
+    // 13600 185 and 165; 64 rows, 4 x 13600 205 and 187, 16 x 4200 (2100 tokens a
+    // share) 221 and 228; where most shares span requests two stay ahead (40 of 80
+    // to 450 tokens 93 and 115).
     bool wide = false, valu = true;
     int requests = 0;
     for (int b = 0; b < r->B; ++b) {
@@ -585,9 +592,9 @@ ss_status plan_chunks(const ss_round *r, int nchunks, const int32_t *len, long t
     }
     W = std::max<long>(1, kTargetWorkgroups / r->Hkv);
     const long share = total / W;
-    const bool many_units = 2 * requests > W || (share < kTinyShare && 4 * requests >= W);
+    const bool many_units = 2 * requests > W || (!wide && share < kTinyShare && 4 * requests >= W);
     const bool six_tiles = r->slots == ss::kBaseSlots && share >= kSixTiles && share < 2 * kMinPiece;
-    const bool two_per_cu = wide || (share < kSmallShare && (valu || many_units));
+    const bool two_per_cu = share < kSmallShare ? valu || many_units : wide;
     if (!two_per_cu && six_tiles && shares_span(ct, r->B, W)) {
       W = std::min(2 * kTargetWorkgroups / r->Hkv, total / kMinPiece);
       if (longest * W > ss::kBaseSlots * total) W = (total + 2 * kMinPiece - 1) / (2 * kMinPiece);

@@ -42,7 +42,11 @@ int main() {
     scenario("4 x 1536 (192 tokens a share, none spans requests)", 4, 32, 8, std::vector<int>(4, 6), std::vector<int>(4, 1536), 2048, 0, layout, 1, 0, 0, 0, 32);
     scenario("2 x 3100, one without tokens between (none spans)", 3, 32, 8, std::vector<int>(3, 6), {3100, 0, 3100}, 4096, 0, layout, 1, 0, 0, 0, 32);
     scenario("2000 and 5000 tokens (one share spans requests)", 2, 32, 8, {6, 6}, {2000, 5000}, 8192, 0, layout, 1, 0, 0, 0, 28);
-    scenario("4 x 4096, 64 rows", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 64);
+    scenario("4 x 4096, 64 rows (512 tokens a share)", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 4096), 4096, 0, layout, 1, 0, 0, 0, 32);
+    scenario("4 x 16383, 64 rows (2047 tokens a share)", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 16383), 16384, 0, layout, 1, 0, 0, 0, 32);
+    scenario("4 x 16384, 64 rows (2048 tokens a share)", 4, 64, 8, std::vector<int>(4, 8), std::vector<int>(4, 16384), 16384, 0, layout, 1, 0, 0, 0, 64);
+    scenario("12 x 1000, 48 rows (375 tokens a share)", 12, 48, 8, std::vector<int>(12, 8), std::vector<int>(12, 1000), 1000, 0, layout, 1, 0, 0, 0, 32);
+    scenario("17 x 1000, 48 rows (over half the shares span requests)", 17, 48, 8, std::vector<int>(17, 8), std::vector<int>(17, 1000), 1000, 0, layout, 1, 0, 0, 0, 64);
     // A workspace allocated for a larger cohort serves a smaller one, which asks for more slots than it holds.
     auto bytes_of = [](int B, int Hq, int Hkv, int n) {
       const std::vector<int> nc(B, n);
